@@ -281,10 +281,10 @@ int sde_gamma(const double* ref, const double* eval, int nx, int ny, int nz, dou
 /* sde_gamma for callers that cannot allocate device memory (code under
  * graph capture, serving loops, harnesses that forbid hipMalloc): the same
  * kernels and the same counts, with the counters and the search list in a
- * fixed scratch array of 4 MiB + 256 bytes that every GPU the library runs on
- * holds until the process ends; it calls no hipMalloc or hipFree.  Voxels
- * failing at the zero offset beyond 2^20 are searched in the first pass
- * (same counts, slower).  Calls on one GPU share its scratch array: calls
+ * fixed scratch array of 4 MiB + 12.25 KiB that every GPU the library runs on
+ * holds until the process ends; it calls no hipMalloc or hipFree.  A grid of
+ * more than 2^20 voxels goes in passes of that many (same counts, a little
+ * slower).  Calls on one GPU share its scratch array: calls
  * that overlap on one GPU (several host threads or streams) race.
  * Arguments, synchronisation and errors as sde_gamma; also SDE_E_INVALID for
  * more than 2^31 voxels. */

@@ -492,45 +492,43 @@ int gamma_check(const double* ref, const double* ev, int nx, int ny, int nz, dou
     return SDE_OK;
 }
 
-// Counters and maximum into buf[0..3], then the two gamma passes with a
-// search list of cap voxel indices; reads the counts back (synchronises the
-// stream).
+// The maximum, then the two gamma passes with a search list of cap voxel
+// indices, on buf (kGammaWords words); reads the counts back once
+// (synchronises the stream).
 int gamma_run(const double* ref, const double* ev, int nx, int ny, int nz, double dx_cm,
               double dy_cm, double dz_cm, double dd, double dta_cm, double thresh, int interp,
               int local, unsigned long long* buf, unsigned* list, unsigned cap,
               int64_t* counts_out) {
     const size_t nvox = (size_t)nx * ny * nz;
     hipStream_t s = cur_stream();
-    unsigned long long host[3] = {0, 0, 0};
-    hipError_t e;
-    if ((e = launch_zero_u64(buf, 4, s)) != hipSuccess ||
-        (e = launch_max(ref, nvox, buf + 2, s)) != hipSuccess ||
-        (e = hipMemcpyAsync(host, buf, sizeof host, hipMemcpyDeviceToHost, s)) != hipSuccess ||
-        (e = hipStreamSynchronize(s)) != hipSuccess)
-        return fail(SDE_E_HIP, hipGetErrorString(e));
-    double mx;
-    std::memcpy(&mx, &host[2], sizeof mx);
-    // the per-octant cells and bounds need the search box inside the 8
-    // cells around a voxel
+    unsigned long long host[16 * kGammaSlots];
+    // the octants' cells and bounds need the search box inside the 8 cells
+    // around a voxel
     const int use_bound =
-        (dta_cm / dx_cm < 1.0 && dta_cm / dy_cm < 1.0 && dta_cm / dz_cm < 1.0) ? 1 : 0;
-    if ((e = launch_gamma(ref, ev, nx, ny, nz, interp, dta_cm, dx_cm, dy_cm, dz_cm, dd,
-                          thresh * mx, mx, local, use_bound, buf, list, cap, s)) != hipSuccess ||
-        (e = hipMemcpyAsync(host, buf, sizeof(unsigned long long) * 2, hipMemcpyDeviceToHost,
-                            s)) != hipSuccess ||
+        (dta_cm / dx_cm <= 1.0 && dta_cm / dy_cm <= 1.0 && dta_cm / dz_cm <= 1.0) ? 1 : 0;
+    hipError_t e;
+    if ((e = launch_max(ref, nvox, buf, s)) != hipSuccess ||
+        (e = launch_gamma(ref, ev, nx, ny, nz, interp, dta_cm, dx_cm, dy_cm, dz_cm, dd, thresh,
+                          1.0 / (dta_cm * dta_cm), local, use_bound, buf, list, cap, s)) !=
+            hipSuccess ||
+        (e = hipMemcpyAsync(host, buf + 16, sizeof host, hipMemcpyDeviceToHost, s)) !=
+            hipSuccess ||
         (e = hipStreamSynchronize(s)) != hipSuccess)
         return fail(SDE_E_HIP, hipGetErrorString(e));
-    counts_out[0] = (int64_t)host[0];
-    counts_out[1] = (int64_t)host[1];
+    counts_out[0] = counts_out[1] = 0;
+    for (int k = 0; k < kGammaSlots; ++k) {
+        counts_out[0] += (int64_t)host[16 * k];
+        counts_out[1] += (int64_t)host[16 * k + 1];
+    }
     return SDE_OK;
 }
 
-// Scratch of sde_gamma_noalloc on each GPU: the four counters, then a
-// search list of kNoallocList voxel indices (voxels beyond it are searched in
-// the first pass).  In host code `scratch` is only a symbol: its device
+// Scratch of sde_gamma_noalloc on each GPU: the counters and partial
+// maxima, then a search list of kNoallocList voxel indices (larger grids go in
+// passes of that many voxels).  In host code `scratch` is only a symbol: its device
 // address comes from hipGetSymbolAddress, once per device.
 constexpr unsigned kNoallocList = 1u << 20;
-constexpr size_t kNoallocCounters = 256;   // bytes before the list
+constexpr size_t kNoallocCounters = (sizeof(unsigned long long) * kGammaWords + 255) / 256 * 256;
 static __device__ __align__(256) unsigned char scratch[kNoallocCounters +
                                                        sizeof(unsigned) * kNoallocList];
 constexpr int kMaxDevices = 64;
@@ -743,9 +741,10 @@ int sde_gamma(const double* ref, const double* ev, int nx, int ny, int nz, doubl
                              counts_out))
         return rc;
     // the counters and the search list, held by the library across calls
-    // (the list grows to the largest grid seen, at most 2^24 entries;
-    // beyond it voxels are searched in the first pass)
-    if (!g.gam_buf) HIP_TRY(hipMalloc((void**)&g.gam_buf, sizeof(unsigned long long) * 4));
+    // (the list grows to the largest grid seen, at most 2^24 entries; larger
+    // grids go in passes of that many voxels)
+    if (!g.gam_buf)
+        HIP_TRY(hipMalloc((void**)&g.gam_buf, sizeof(unsigned long long) * kGammaWords));
     const unsigned want = (unsigned)std::min<size_t>((size_t)nx * ny * nz, (size_t)1 << 24);
     if (want > g.gam_cap) {
         dfree(g.gam_list);

@@ -163,16 +163,21 @@ hipError_t launch_transport(const KParams& p, int grid, int block, size_t lds_by
 hipError_t launch_convert(unsigned long long* tally, int n_rep, const uint2* vox, size_t nvox,
                           double inv_scale, double voxel_cm3, double* dose,
                           unsigned long long* ledger, hipStream_t s);
-// gamma_kernels.hip: offsets on the lattice of spacing dta / interp
-// (interp <= 50) within dta; use_bound needs dta below a voxel on every axis.
-// counts[4] = {evaluated, passed, maximum bits, list length} (counts[0], [1]
-// and [3] zero on entry); list: cap voxel indices of scratch.
+// gamma_kernels.hip: launch_max writes partial maxima of the reference into
+// buf (kGammaWords words of scratch, with the counters, which it zeroes), then
+// launch_gamma evaluates offsets on the lattice of spacing dta / interp
+// (interp <= 50) within dta above thresh times that maximum; use_bound needs
+// dta at most a voxel on every axis; inv_dta2 = 1 / dta^2; list: cap voxel
+// indices of scratch.  The results are sums over the kGammaSlots lines of 16
+// words from buf + 16: word 0 evaluated, word 1 passed.
+constexpr int kGammaSlots = 32, kGammaMaxParts = 1024;
+constexpr int kGammaWords = 16 * (1 + kGammaSlots) + kGammaMaxParts;
 hipError_t launch_gamma(const double* ref, const double* ev, int nx, int ny, int nz, int interp,
-                        double dta, double dx, double dy, double dz, double dd, double thr_abs,
-                        double max_ref, int local, int use_bound, unsigned long long* counts,
+                        double dta, double dx, double dy, double dz, double dd, double thresh,
+                        double inv_dta2, int local, int use_bound, unsigned long long* buf,
                         unsigned* list, unsigned cap, hipStream_t s);
 hipError_t launch_zero_u64(unsigned long long* p, int n, hipStream_t s);
-hipError_t launch_max(const double* a, size_t n, unsigned long long* out_bits, hipStream_t s);
+hipError_t launch_max(const double* a, size_t n, unsigned long long* buf, hipStream_t s);
 hipError_t launch_sbm_polar(const float* t, const float* u, const float* z, int n, float* c,
                             float* s_out, hipStream_t s);
 hipError_t transport_kernel_attributes(size_t lds_bytes);
