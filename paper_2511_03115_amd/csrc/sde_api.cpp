@@ -452,6 +452,16 @@ int make_plan(const sde_beam* beam, const sde_phantom* ph, uint64_t n_histories,
     kp.jump_batch = jump_batch;
     kp.nan_h = L.nan_history ? L.nan_history - 1 : ~0ull;
     kp.claim_chunk = claim_chunk;
+    // every wave starts on a range of its own; with fewer histories than that
+    // holds, an even share for as many waves per SIMD as they fill
+    const unsigned long long waves = (unsigned long long)grid * (block / 64);
+    const unsigned long long simds = 4ull * std::max(1, g.n_cu);
+    const unsigned long long used =
+        std::min(waves, (total + 64 * simds - 1) / (64 * simds) * simds);
+    kp.first_chunk = std::min<unsigned long long>(claim_chunk, (total + used - 1) / used);
+    kp.dyn0 = waves * kp.first_chunk;
+    kp.share_shift = 1;
+    while ((1ull << kp.share_shift) < 2 * waves) ++kp.share_shift;
     // End-of-range screen: for E above ec[m] the residual range exceeds the
     // step at every voxel of material m (densest voxel, 0.1 % margin); below
     // it the kernel decides in FP64.

@@ -62,12 +62,12 @@ __host__ __device__ inline int tile_slot(int ix, int iy, int iz, int x0, int y0,
 // Lattice interval i in [0, n_e - 2] of lattice coordinate t (rows i and
 // i + 1 are read).
 __host__ __device__ inline int lattice_interval(float t, int n_e) {
-    const int c = (int)t, i = c < 0 ? 0 : (c > n_e - 2 ? n_e - 2 : c);
+    const int c = (int)t, lim = n_e - 2, m = c < lim ? c : lim, i = m > 0 ? m : 0;
     SDE_CHECK(i >= 0 && i + 1 < n_e, "t=%.9g n_e=%d i=%d", (double)t, n_e, i);
     return i;
 }
 __host__ __device__ inline int lattice_interval(double t, int n_e) {
-    const int c = (int)t, i = c < 0 ? 0 : (c > n_e - 2 ? n_e - 2 : c);
+    const int c = (int)t, lim = n_e - 2, m = c < lim ? c : lim, i = m > 0 ? m : 0;
     SDE_CHECK(i >= 0 && i + 1 < n_e, "t=%.17g n_e=%d i=%d", t, n_e, i);
     return i;
 }

@@ -142,11 +142,14 @@ struct KParams {
     unsigned long long rep_stride;   // nvox
     int n_rep, pad6;
     unsigned long long* ledger;      // [kLedgerN]
-    unsigned long long* counter;     // next history
+    unsigned long long* counter;     // histories claimed beyond the first ranges
+    unsigned long long first_chunk;  // histories of a wave's first range, by wave number
+    unsigned long long dyn0;         // end of the first ranges: the counter counts from here
     float* rec;                      // optional [n_hist][12] per-history records
     float ec[kMaxMat];               // end-of-range screen energy per material (this phantom)
     int jump_batch;                  // finish pending jumps when this many lanes wait
-    int claim_chunk;                 // history indices a wave takes from the counter at once
+    int claim_chunk;                 // most history indices a wave takes from the counter at once
+    int share_shift;                 // 2^share_shift >= 2 waves: left >> share_shift is half a share
     int refill;
     int tile_nx, tile_ny, tile_nz, tile_x0, tile_y0, tile_z0, pad4;
     unsigned long long nan_h;        // test hook: this history starts with a NaN direction

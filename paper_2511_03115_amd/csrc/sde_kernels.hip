@@ -116,12 +116,14 @@ __device__ __forceinline__ uint4 philox(uint32_t c0, uint32_t c1, uint32_t c2, u
 
 // (2k+1) 2^-24 from the top 23 bits: exact in FP32 and FP64, never 0 or 1.
 template <class R>
-__device__ __forceinline__ R u_hi(uint32_t w) { return ((R)(w >> 9) + R(0.5)) * R(0x1p-23); }
+__device__ __forceinline__ R u_hi(uint32_t w) {
+    return RM<R>::fma((R)(w >> 9), R(0x1p-23), R(0x1p-24));
+}
 // Same from the 23 low bits that u_hi leaves unused in three words.
 template <class R>
 __device__ __forceinline__ R u_lo(uint32_t a, uint32_t b, uint32_t c) {
     const uint32_t k = (a & 0x1FFu) | ((b & 0x1FFu) << 9) | ((c & 0x1Fu) << 18);
-    return ((R)k + R(0.5)) * R(0x1p-23);
+    return RM<R>::fma((R)k, R(0x1p-23), R(0x1p-24));
 }
 
 // cos and sin of a polar angle given its square.  float: Taylor in theta^2
@@ -277,13 +279,17 @@ __device__ __noinline__ CosSin<R> sbm_large(double td, double ud) {
 // Duff et al. (JCGT 2017) orthonormal basis of d.
 template <class R>
 __device__ __forceinline__ void turn(R& dx, R& dy, R& dz, R ct, R st, R cp, R sp) {
+    // the fused products are spelled out, so that every caller rounds alike
+#pragma clang fp contract(off)
+    using M = RM<R>;
     const R sg = copysign(R(1), dz);
-    const R a = -RM<R>::rcp(sg + dz);   // |sg + dz| >= 1
+    const R a = -M::rcp(sg + dz);   // |sg + dz| >= 1
     const R b = dx * dy * a;
-    const R b1x = R(1) + sg * dx * dx * a, b1y = sg * b, b1z = -sg * dx;
-    const R b2x = b, b2y = sg + dy * dy * a, b2z = -dy;
-    const R ex = cp * b1x + sp * b2x, ey = cp * b1y + sp * b2y, ez = cp * b1z + sp * b2z;
-    const R nx = ct * dx + st * ex, ny = ct * dy + st * ey, nz = ct * dz + st * ez;
+    const R b1x = M::fma(sg * dx * dx, a, R(1)), b1y = sg * b, b1z = -sg * dx;
+    const R b2y = M::fma(dy * dy, a, sg);   // b2x = b, b2z = -dy
+    const R ex = M::fma(sp, b, cp * b1x), ey = M::fma(cp, b1y, sp * b2y),
+            ez = M::fma(cp, b1z, -(sp * dy));
+    const R nx = M::fma(ct, dx, st * ex), ny = M::fma(ct, dy, st * ey), nz = M::fma(ct, dz, st * ez);
     dx = nx;
     dy = ny;
     dz = nz;
@@ -362,6 +368,9 @@ __device__ __forceinline__ void score(const KParams& P, const KScal<R>& S,
                                       unsigned long long* tile, unsigned long long* rep, Acc<R>& a,
                                       R x, R y, R z, R e, R wsc, long long& esc,
                                       bool check = true) {
+    // the weighted energy is rounded before it is added, whatever the compiler
+    // makes of the code around
+#pragma clang fp contract(off)
     if (check && !inside(S, x, y, z)) {
         esc += fixp(e, wsc);
         return;
@@ -897,10 +906,11 @@ __device__ __forceinline__ double range_g64(const KParams& P, int mat, double E)
 // last jump step, 0, 0}: end 1 = end of range, 2 = left the phantom,
 // 3 = below e_min, 4 = step limit, 5 = source; E is the energy at the end
 // event (before absorption).
+template <bool kRec>
 __device__ __forceinline__ void record(const KParams& P, unsigned long long h, float e0,
                                       unsigned steps, unsigned jumps, int end, float x, float y,
                                       float z, float e, int j1, int j2) {
-    if (!P.rec) return;
+    if (!kRec || !P.rec) return;
     float* r = P.rec + h * 12;
     r[0] = e0;
     r[1] = (float)steps;
@@ -922,7 +932,13 @@ __device__ __forceinline__ unsigned long long wave_sum(unsigned long long v) {
     return v;
 }
 
-enum : int { kDead = 0, kStep = 1, kJump = 2, kEnd = 3 };
+// Steps a wave takes between two looks at its waiting lanes (refill, jumps,
+// ends of range, the step limit).  The look's ballots and tests cost a tenth of
+// a step; a lane that stops in between idles until the next one.  1e7 histories
+// of 150 MeV in water: 33.6, 32.4, 31.8, 31.4, 31.2, 31.5, 31.9 ms with 1, 2,
+// 3, 4, 6, 8, 12.
+constexpr unsigned kSub = 6;
+enum : int { kDead = 0, kStep = 1, kJump = 2, kEnd = 3, kTurn = 4 };
 
 __device__ __forceinline__ const SpotDev& spot_at(const KParams& P, int i, float) {
     return P.spots[i];
@@ -936,7 +952,16 @@ __device__ __forceinline__ const SpotDev64& spot_at(const KParams& P, int i, dou
 // read them from P.flags.  kNuc: the elastic nuclear terms are compiled in
 // (their double-precision hydrogen functions are out of line, and the calls
 // cost registers, so only the instances launched with such data have them).
-template <class R, unsigned kFixed, bool kNuc>
+// kRec: per-history records are compiled in; the method's own instances come
+// with and without, as their registers and tests cost a launch without them 1 %.
+//
+// Bound by VALU issue.  What the step loop does to issue less: several steps
+// per look at the waiting lanes (kSub), the medium's constants and table offset
+// read once per voxel, one exit test, random uniforms by one fused
+// multiply-add, no step counter beside the step index.  1e7 histories of 150
+// MeV in water 33.9 -> 29.8 ms, 1000 spots on 2 mm voxels (2e6 histories) 7.33
+// -> 6.58 ms; 2.21e10 -> 2.11e10 VALU and 9.6e9 -> 7.1e9 scalar instructions.
+template <class R, unsigned kFixed, bool kNuc, bool kRec>
 __global__ void __launch_bounds__(1024) k_transport(KParams P) {
     using M = RM<R>;
     const KScal<R>& S = scal<R>(P);
@@ -945,9 +970,11 @@ __global__ void __launch_bounds__(1024) k_transport(KParams P) {
     float4* tab = reinterpret_cast<float4*>(smem);
     const int ntab = P.n_mat * P.n_e;
     for (int i = threadIdx.x; i < ntab; i += blockDim.x) tab[i] = P.hot[i];
-    float4* matc = tab + ntab;   // per material {zoa, Bethe log offset, end-of-range screen, 0}
+    // per material {zoa, Bethe log offset, end-of-range screen, table offset}
+    float4* matc = tab + ntab;
     for (int i = threadIdx.x; i < P.n_mat; i += blockDim.x)
-        matc[i] = make_float4(P.mats[i].zoa, P.mats[i].log_pre, P.ec[i], 0.0f);
+        matc[i] = make_float4(P.mats[i].zoa, P.mats[i].log_pre, P.ec[i],
+                              __int_as_float(i * P.n_e));
     unsigned long long* tile =
         reinterpret_cast<unsigned long long*>(smem + (size_t)(ntab + P.n_mat) * 16);
     const int tile_n = P.tile_nx * P.tile_ny * P.tile_nz;
@@ -964,13 +991,20 @@ __global__ void __launch_bounds__(1024) k_transport(KParams P) {
     int state = kDead;
     bool end_checked = false;   // the residual range exceeded the step: skip the screen once
     bool more = true;   // wave-uniform: the work counter may still hold histories
-    unsigned long long q_next = 0, q_end = 0;   // wave-local range of history indices
+    // wave-local range of history indices; the first one is the wave's by its
+    // number (the workgroups' first waves, then their second ones, ...: few
+    // histories spread over all CUs), the rest come from the work counter
+    const unsigned wid =
+        __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) * gridDim.x + blockIdx.x);
+    unsigned long long q_next = (unsigned long long)wid * P.first_chunk,
+                       q_end = q_next + P.first_chunk;
 
     unsigned long long h = 0;
     unsigned n = 0;
     R E = R(0), rx = R(0), ry = R(0), rz = R(0), ox = R(0), oy = R(0), oz = R(1), wsc = R(0);
     int vcache = -1, mat = 0;
     R rho = R(1), e0 = R(0);
+    float4 mc = make_float4(0.f, 0.f, 0.f, 0.f);   // matc[mat], read when the voxel changes
     // pending jump: state energy, material, density and step index at the jump
     R ej = R(0), rhoj = R(1);
     int matj = 0;
@@ -984,6 +1018,7 @@ __global__ void __launch_bounds__(1024) k_transport(KParams P) {
     bool sbm_pend = false;
     R sbm_t = R(0), sbm_u = R(0), sbm_ph = R(0);
 
+    const unsigned max_n = (unsigned)min(P.max_steps, 0xFFFFFF00ll);
     for (;;) {
         if (state == kDead) acc_flush(tile, rep, acc);
         // ---------------- small-angle turns in the exact regime ----------------
@@ -999,32 +1034,43 @@ __global__ void __launch_bounds__(1024) k_transport(KParams P) {
                 oy *= inv;
                 oz *= inv;
             }
+            if (state == kTurn) state = kStep;
             sbm_pend = false;
         }
         // ---------------- refill idle lanes ----------------
         // History indices come from a wave-local range [q_next, q_end) that is
         // refilled a chunk at a time from the global counter (one atomic per
-        // chunk); the range is wave-uniform.
+        // chunk; none when the first ranges cover every history: 4096 waves
+        // asking at once wait 50 us on it); the range is wave-uniform.
         const unsigned long long dead = __ballot(state == kDead);
         const int ndead = __popcll(dead);
         if (more && (ndead >= P.refill || ndead == 64)) {
             const int leader = __ffsll((long long)dead) - 1;
             const unsigned long long lim = q_end < P.n_hist ? q_end : P.n_hist;
-            const unsigned long long avail = q_next < lim ? lim - q_next : 0ull;
-            unsigned long long base = 0;
-            const bool claim = avail < (unsigned long long)ndead;
-            if (claim) {
-                if (lane == leader) base = atomicAdd(P.counter, (unsigned long long)P.claim_chunk);
+            const unsigned avail = q_next < lim ? (unsigned)(lim - q_next) : 0u;
+            unsigned long long base = P.n_hist;
+            unsigned chunk = 0;
+            const bool claim = avail < (unsigned)ndead;
+            if (claim && P.dyn0 < P.n_hist) {
+                // half a fair share of what was left at the wave's last claim,
+                // so that no wave sits on a chunk when the others run dry
+                const unsigned long long left = P.n_hist - (q_end < P.dyn0 ? P.dyn0 : lim);
+                chunk = (unsigned)min(max(left >> P.share_shift, 8ull),
+                                      (unsigned long long)P.claim_chunk);
+                if (lane == leader) base = P.dyn0 + atomicAdd(P.counter, (unsigned long long)chunk);
                 base = __shfl(base, leader);
             }
             if (state == kDead) {
-                const unsigned long long rank = __popcll(dead & ((1ull << lane) - 1ull));
-                const unsigned long long hh = rank < avail ? q_next + rank : base + (rank - avail);
+                const unsigned rank = __popcll(dead & ((1ull << lane) - 1ull));
+                const unsigned long long hh = rank < avail             ? q_next + rank
+                                              : rank - avail < chunk ? base + (rank - avail)
+                                                                     : P.n_hist;
                 if (hh < P.n_hist) {
                     // Source: spot by cumulative count in claim order; the
                     // history's index h is its index in the caller's spot
                     // order.  Box-Muller pairs from block (h, 2^32-1, 0):
                     // (w0, w1) lateral, (w2, w3) energy.
+                    l_steps += n;   // the lane's last history
                     n = 0;
                     int lo = 0, hi = P.n_spots - 1;
                     while (lo < hi) {
@@ -1055,11 +1101,11 @@ __global__ void __launch_bounds__(1024) k_transport(KParams P) {
                     l_e0 += fixp(E, wsc);
                     if (!inside(S, rx, ry, rz)) {
                         l_esc += fixp(E, wsc);
-                        record(P, h, (float)e0, 0, 0, 5, (float)rx, (float)ry, (float)rz, (float)E,
+                        record<kRec>(P, h, (float)e0, 0, 0, 5, (float)rx, (float)ry, (float)rz, (float)E,
                                -1, -1);
                     } else if (E < S.e_min) {
                         score(P, S, tile, rep, acc, rx, ry, rz, E, wsc, l_esc);
-                        record(P, h, (float)e0, 0, 0, 5, (float)rx, (float)ry, (float)rz, (float)E,
+                        record<kRec>(P, h, (float)e0, 0, 0, 5, (float)rx, (float)ry, (float)rz, (float)E,
                                -1, -1);
                     } else {
                         int ix, iy, iz;
@@ -1068,13 +1114,14 @@ __global__ void __launch_bounds__(1024) k_transport(KParams P) {
                         const uint2 pk = P.vox[vcache];
                         rho = (R)__uint_as_float(pk.x);
                         mat = (int)pk.y;
+                        mc = matc[mat];
                         state = kStep;
                     }
                 }
             }
             if (claim) {
-                q_next = base + ((unsigned long long)ndead - avail);
-                q_end = base + (unsigned long long)P.claim_chunk;
+                q_next = base + min((unsigned)ndead - avail, chunk);
+                q_end = base + chunk;
                 if (base >= P.n_hist) more = false;
             } else {
                 q_next += (unsigned long long)ndead;
@@ -1109,7 +1156,7 @@ __global__ void __launch_bounds__(1024) k_transport(KParams P) {
                 state = kStep;
                 if (!__builtin_isfinite(En * ox)) {   // the lane guard, as after a step
                     l_bad += fixp(E, wsc);
-                    record(P, h, (float)e0, n, hj, 6, (float)rx, (float)ry, (float)rz, (float)E,
+                    record<kRec>(P, h, (float)e0, n, hj, 6, (float)rx, (float)ry, (float)rz, (float)E,
                            j1, j2);
                     state = kDead;
                 } else {
@@ -1117,12 +1164,12 @@ __global__ void __launch_bounds__(1024) k_transport(KParams P) {
                     E = En;
                     if (!inside(S, rx, ry, rz)) {
                         l_esc += fixp(E, wsc);
-                        record(P, h, (float)e0, n, hj, 2, (float)rx, (float)ry, (float)rz,
+                        record<kRec>(P, h, (float)e0, n, hj, 2, (float)rx, (float)ry, (float)rz,
                                (float)E, j1, j2);
                         state = kDead;
                     } else if (E < S.e_min) {
                         score(P, S, tile, rep, acc, rx, ry, rz, E, wsc, l_esc);
-                        record(P, h, (float)e0, n, hj, 3, (float)rx, (float)ry, (float)rz,
+                        record<kRec>(P, h, (float)e0, n, hj, 3, (float)rx, (float)ry, (float)rz,
                                (float)E, j1, j2);
                         state = kDead;
                     }
@@ -1143,11 +1190,11 @@ __global__ void __launch_bounds__(1024) k_transport(KParams P) {
                         const R hr = (R)(0.5 * rres);
                         score(P, S, tile, rep, acc, M::fma(ox, hr, rx), M::fma(oy, hr, ry),
                               M::fma(oz, hr, rz), E, wsc, l_esc);
-                        l_steps++;
                         const R fr = (R)rres;
-                        record(P, h, (float)e0, n + 1, hj, 1, (float)M::fma(ox, fr, rx),
+                        record<kRec>(P, h, (float)e0, n + 1, hj, 1, (float)M::fma(ox, fr, rx),
                                (float)M::fma(oy, fr, ry), (float)M::fma(oz, fr, rz), (float)E,
                                j1, j2);
+                        n++;
                         state = kDead;
                     } else {
                         state = kStep;
@@ -1156,233 +1203,241 @@ __global__ void __launch_bounds__(1024) k_transport(KParams P) {
                 }
             }
         }
-        if (state != kStep) continue;
-
-        // ---------------- one step of Eq. (VSDE) ----------------
-        if ((long long)n >= P.max_steps) {
+        // ---------------- steps of Eq. (VSDE) ----------------
+        if (state == kStep && n >= max_n) {
             atomicAdd(&P.ledger[4], (unsigned long long)fixp(E, wsc));
-            record(P, h, (float)e0, n, hj, 4, (float)rx, (float)ry, (float)rz, (float)E, j1, j2);
+            record<kRec>(P, h, (float)e0, n, hj, 4, (float)rx, (float)ry, (float)rz, (float)E, j1,
+                         j2);
             state = kDead;
-            continue;
         }
-        const float4 mc = matc[mat];
+        const int reps = __ballot(state == kStep && n + kSub > max_n) ? 1 : (int)kSub;
+        for (int sub = 0; sub < reps; ++sub) {
+            if (state != kStep) continue;
 
-        // End of range: residual range within one step, decided in FP64 in the
-        // batch above; the FP32 screen E <= ec(material) is exact-safe (ec
-        // bounds the energy whose range fits a step at the densest voxel of
-        // that material).
-        if ((flags & kEor) && E <= (R)mc.z && !end_checked) {
-            state = kEnd;
-            continue;
-        }
-        end_checked = false;
+            // End of range: residual range within one step, decided in FP64 in the
+            // batch above; the FP32 screen E <= ec(material) is exact-safe (ec
+            // bounds the energy whose range fits a step at the densest voxel of
+            // that material).
+            if ((flags & kEor) && E <= (R)mc.z && !end_checked) {
+                state = kEnd;
+                continue;
+            }
+            end_checked = false;
 
-        const R lnE = M::lg(E);
-        const R tl = (lnE - S.ln_e_lo) * S.inv_dln;
-        const int li = lattice_interval(tl, P.n_e);
-        const R lf = tl - (R)li;
-        float4 ta, tb;
-        if constexpr (!M::f64) {
-            ta = tab[mat * P.n_e + li];
-            tb = tab[mat * P.n_e + li + 1];
-        }
-        const uint4 w = philox((uint32_t)h, (uint32_t)(h >> 32), n, 0u, k0, k1);
+            const R tr = M::lg(E) - S.ln_e_lo;
+            const R tl = tr * S.inv_dln;
+            const int li = lattice_interval(tl, P.n_e);
+            // (the method's instances have always fused these, and below the
+            // renormalisation's sum in this order: their tallies stay the same
+            // to the last bit)
+            const R lf = kFixed ? M::fma(tr, S.inv_dln, -(R)li) : tl - (R)li;
+            float4 ta, tb;
+            if constexpr (!M::f64) {
+                const float4* row = tab + (__float_as_int(mc.w) + li);
+                ta = row[0];
+                tb = row[1];
+            }
+            const uint4 w = philox((uint32_t)h, (uint32_t)(h >> 32), n, 0u, k0, k1);
 
-        // Continuous loss, Eq. (bethbloch) with Bragg additivity; clamped
-        // straggling, Eq. (energystraggling), B_n ~ N(0, Delta).
-        R zoa, log_pre;
-        if constexpr (M::f64) {
-            zoa = P.mats64[mat].zoa;
-            log_pre = P.mats64[mat].log_pre;
-        } else {
-            zoa = mc.x;
-            log_pre = mc.y;
-        }
-        const R p2 = E * (E + R(2) * (R)kMp);
-        const R g = E + (R)kMp;
-        const R b2 = p2 * M::rcp(g * g);
-        R s1 = R(0);
-        if (flags & kLoss) {
-            const R L = log_pre + M::lg(p2) - b2;
-            s1 = rho * S.c_bethe * zoa * L * M::rcp(b2);
-        }
-        const R a = s1 * S.step;
-        R X = R(0);
-        if (flags & kStraggle) {
-            const R gm = g * (R(1) / (R)kMp);
-            const R var = rho * S.c_strag * zoa * gm * gm * (R(1) - R(0.5) * b2);
-            const R zE = M::sq(R(-2) * M::lg(u_hi<R>(w.x))) * M::cosr(u_hi<R>(w.y));
-            X = fmin(fmax(M::sq(var) * S.sqrt_step * zE, -a), a);
-        }
-        const R Ep = fmax(E - a + X, R(0));
+            // Continuous loss, Eq. (bethbloch) with Bragg additivity; clamped
+            // straggling, Eq. (energystraggling), B_n ~ N(0, Delta).
+            R zoa, log_pre;
+            if constexpr (M::f64) {
+                zoa = P.mats64[mat].zoa;
+                log_pre = P.mats64[mat].log_pre;
+            } else {
+                zoa = mc.x;
+                log_pre = mc.y;
+            }
+            const R p2 = E * (E + R(2) * (R)kMp);
+            const R g = E + (R)kMp;
+            const R b2 = p2 * M::rcp(g * g);
+            R s1 = R(0);
+            if (flags & kLoss) {
+                const R L = log_pre + M::lg(p2) - b2;
+                s1 = rho * S.c_bethe * zoa * L * M::rcp(b2);
+            }
+            const R a = s1 * S.step;
+            R X = R(0);
+            if (flags & kStraggle) {
+                const R gm = g * (R(1) / (R)kMp);
+                const R var = rho * S.c_strag * zoa * gm * gm * (R(1) - R(0.5) * b2);
+                const R zE = M::sq(R(-2) * M::lg(u_hi<R>(w.x))) * M::cosr(u_hi<R>(w.y));
+                X = fmin(fmax(M::sq(var) * S.sqrt_step * zE, -a), a);
+            }
+            const R Ep = fmax(E - a + X, R(0));
 
-        // Jump test: none with probability exp(-Delta sigma).  float: elastic
-        // rate (Rutherford + Mott) = el_E2 / E^2 with el_E2 smooth in ln E,
-        // inelastic rate linear on the lattice; double: the elastic rate from
-        // its closed form at E.
-        bool jumped = false;
-        if (flags & (kElastic | kInelastic)) {
-            R rate;
-            if ((flags & kEcut) && (flags & kElastic)) {
-                // the cut 2.5 sigma(E) at this step's medium and density
-                const Cut<R> cut = energy_cut(S, ld_sig2z(P, S, tab, mat, rho, E, li, lf));
-                R el, ne_rate;
-                R nucl;
-                if constexpr (M::f64) {
+            // Jump test: none with probability exp(-Delta sigma).  float: elastic
+            // rate (Rutherford + Mott) = el_E2 / E^2 with el_E2 smooth in ln E,
+            // inelastic rate linear on the lattice; double: the elastic rate from
+            // its closed form at E.
+            bool jumped = false;
+            if (flags & (kElastic | kInelastic)) {
+                R rate;
+                if ((flags & kEcut) && (flags & kElastic)) {
+                    // the cut 2.5 sigma(E) at this step's medium and density
+                    const Cut<R> cut = energy_cut(S, ld_sig2z(P, S, tab, mat, rho, E, li, lf));
+                    R el, ne_rate;
+                    R nucl;
+                    if constexpr (M::f64) {
+                        const MatDev64& md = P.mats64[mat];
+                        el = md.c_ruth0 * (cut.T - 0.5);
+                        if (md.c_mott != 0.0)
+                            el += md.c_mott * mott_bracket(S, cut, S.eta_pre / ::sqrt(E));
+                        const double2 ha = P.hot64[(size_t)mat * P.n_e + li];
+                        const double2 hb = P.hot64[(size_t)mat * P.n_e + li + 1];
+                        ne_rate = ::fma(lf, hb.x - ha.x, ha.x);
+                        nucl = nuclear_sum(P, S, md, E, li, lf, cut);
+                    } else {
+                        const MatDev& md = P.mats[mat];
+                        el = md.c_ruth0 * (cut.T - 0.5f);
+                        if (md.c_mott != 0.0f)
+                            el += md.c_mott * mott_bracket(S, cut, S.eta_pre * M::rsq(E));
+                        ne_rate = fmaf(lf, tb.z - ta.z, ta.z);
+                        nucl = R(0);
+                        if constexpr (kNuc) nucl = nuclear_sum(P, S, md, E, li, lf, cut);
+                    }
+                    rate = el / (E * E) + nucl + ((flags & kInelastic) ? ne_rate : R(0));
+                } else if constexpr (M::f64) {
                     const MatDev64& md = P.mats64[mat];
-                    el = md.c_ruth0 * (cut.T - 0.5);
-                    if (md.c_mott != 0.0)
-                        el += md.c_mott * mott_bracket(S, cut, S.eta_pre / ::sqrt(E));
                     const double2 ha = P.hot64[(size_t)mat * P.n_e + li];
                     const double2 hb = P.hot64[(size_t)mat * P.n_e + li + 1];
-                    ne_rate = ::fma(lf, hb.x - ha.x, ha.x);
-                    nucl = nuclear_sum(P, S, md, E, li, lf, cut);
+                    rate = R(0);
+                    if (flags & kElastic) {
+                        R el = md.c_ruth;
+                        if (md.c_mott != 0.0)
+                            el += md.c_mott * mott_bracket(S, fixed_cut(S), S.eta_pre / ::sqrt(E));
+                        rate += el / (E * E) + nuclear_sum(P, S, md, E, li, lf, fixed_cut(S));
+                    }
+                    if (flags & kInelastic) rate += ::fma(lf, hb.x - ha.x, ha.x);
                 } else {
-                    const MatDev& md = P.mats[mat];
-                    el = md.c_ruth0 * (cut.T - 0.5f);
-                    if (md.c_mott != 0.0f)
-                        el += md.c_mott * mott_bracket(S, cut, S.eta_pre * M::rsq(E));
-                    ne_rate = fmaf(lf, tb.z - ta.z, ta.z);
-                    nucl = R(0);
-                    if constexpr (kNuc) nucl = nuclear_sum(P, S, md, E, li, lf, cut);
+                    const float el_e2 = fmaf(lf, tb.w - ta.w, ta.w);
+                    const float ne_rate = fmaf(lf, tb.z - ta.z, ta.z);
+                    rate = ((flags & kElastic) ? el_e2 * M::rcp(E * E) : 0.0f) +
+                           ((flags & kInelastic) ? ne_rate : 0.0f);
                 }
-                rate = el / (E * E) + nucl + ((flags & kInelastic) ? ne_rate : R(0));
-            } else if constexpr (M::f64) {
-                const MatDev64& md = P.mats64[mat];
-                const double2 ha = P.hot64[(size_t)mat * P.n_e + li];
-                const double2 hb = P.hot64[(size_t)mat * P.n_e + li + 1];
-                rate = R(0);
-                if (flags & kElastic) {
-                    R el = md.c_ruth;
-                    if (md.c_mott != 0.0)
-                        el += md.c_mott * mott_bracket(S, fixed_cut(S), S.eta_pre / ::sqrt(E));
-                    rate += el / (E * E) + nuclear_sum(P, S, md, E, li, lf, fixed_cut(S));
+                const R lam = S.step * rho * rate;
+                R pj;
+                if constexpr (M::f64) {
+                    pj = -::expm1(-lam);
+                } else {
+                    pj = lam * fmaf(-0.5f * lam,
+                                    fmaf(-lam * (1.0f / 3.0f), fmaf(-0.25f, lam, 1.0f), 1.0f), 1.0f);
+                    if (!(lam < 0.05f)) pj = 1.0f - __expf(-lam);
                 }
-                if (flags & kInelastic) rate += ::fma(lf, hb.x - ha.x, ha.x);
-            } else {
-                const float el_e2 = fmaf(lf, tb.w - ta.w, ta.w);
-                const float ne_rate = fmaf(lf, tb.z - ta.z, ta.z);
-                rate = ((flags & kElastic) ? el_e2 * M::rcp(E * E) : 0.0f) +
-                       ((flags & kInelastic) ? ne_rate : 0.0f);
+                jumped = u_lo<R>(w.x, w.y, w.z) < pj;
             }
-            const R lam = S.step * rho * rate;
-            R pj;
-            if constexpr (M::f64)
-                pj = -::expm1(-lam);
-            else
-                pj = lam < 0.05f
-                    ? lam * fmaf(-0.5f * lam, fmaf(-lam * (1.0f / 3.0f), fmaf(-0.25f, lam, 1.0f), 1.0f), 1.0f)
-                    : 1.0f - __expf(-lam);
-            jumped = u_lo<R>(w.x, w.y, w.z) < pj;
-        }
 
-        // Deposit E_n - E' at the step midpoint (pre-step direction), move.
-        // Both R_n and, when in_next, R_{n+1} lie in the box, and so does the
-        // midpoint: its inside test is needed only when R_{n+1} left.
-        const R nx = M::fma(ox, S.step, rx), ny = M::fma(oy, S.step, ry), nz = M::fma(oz, S.step, rz);
-        const bool in_next = inside(S, nx, ny, nz);
-        score(P, S, tile, rep, acc, M::fma(ox, S.half_step, rx), M::fma(oy, S.half_step, ry),
-              M::fma(oz, S.half_step, rz), E - Ep, wsc, l_esc, !in_next);
-        rx = nx;
-        ry = ny;
-        rz = nz;
-        uint2 pk_next = make_uint2(0u, 0u);
-        int v_next = vcache;
-        if (in_next) {   // prefetch the next voxel while the direction is updated
-            int ix, iy, iz;
-            voxel3(P, S, rx, ry, rz, ix, iy, iz);
-            v_next = voxel_index(ix, iy, iz, P.nx, P.ny, P.nz);
-            if (v_next != vcache) pk_next = P.vox[v_next];
-        }
+            // Deposit E_n - E' at the step midpoint (pre-step direction), move.
+            // Both R_n and, when in_next, R_{n+1} lie in the box, and so does the
+            // midpoint: its inside test is needed only when R_{n+1} left.
+            const R nx = M::fma(ox, S.step, rx), ny = M::fma(oy, S.step, ry), nz = M::fma(oz, S.step, rz);
+            const bool in_next = inside(S, nx, ny, nz);
+            score(P, S, tile, rep, acc, M::fma(ox, S.half_step, rx), M::fma(oy, S.half_step, ry),
+                  M::fma(oz, S.half_step, rz), E - Ep, wsc, l_esc, !in_next);
+            rx = nx;
+            ry = ny;
+            rz = nz;
+            uint2 pk_next = make_uint2(0u, 0u);
+            int v_next = vcache;
+            if (in_next) {   // prefetch the next voxel while the direction is updated
+                int ix, iy, iz;
+                voxel3(P, S, rx, ry, rz, ix, iy, iz);
+                v_next = voxel_index(ix, iy, iz, P.nx, P.ny, P.nz);
+                if (v_next != vcache) pk_next = P.vox[v_next];
+            }
 
-        // Small-angle diffusion over time t = sigma^2 Delta / z, sigma the
-        // Lynch-Dahl width: the spherical Brownian motion law (switch kSbm;
-        // the lineage count's normal is the sine partner of Z_E's
-        // Box-Muller pair) or the geodesic Gaussian step of per-axis
-        // variance t.
-        if (flags & kMcs) {
-            R sig2;
-            if constexpr (M::f64) {
-                sig2 = ld_time64(P.mats64[mat], S, rho, E);
-            } else {
-                const float A1 = fmaf(lf, tb.x - ta.x, ta.x);
-                const float A2 = fmaf(lf, tb.y - ta.y, ta.y);
-                const float nu = rho * A2;
-                const float br = (1.0f + M::rcp(nu)) * M::lg(1.0f + nu) - 1.0f;
-                sig2 = rho * A1 * br;
-            }
-            R ct = R(1), st = R(0);
-            bool now = true;
-            if (flags & kSbm) {
-                if (sig2 < SbmSwitch<R>::t) {
-                    const R zM = M::sq(R(-2) * M::lg(u_hi<R>(w.x))) * M::sinr(u_hi<R>(w.y));
-                    sbm_small(sig2, zM, u_hi<R>(w.z), ct, st);
-                } else {   // exact regime: drawn at the top of the loop
-                    now = false;
-                    sbm_pend = true;
-                    sbm_t = sig2;
-                    sbm_u = u_hi<R>(w.z);
-                    sbm_ph = u_hi<R>(w.w);
+            // Small-angle diffusion over time t = sigma^2 Delta / z, sigma the
+            // Lynch-Dahl width: the spherical Brownian motion law (switch kSbm;
+            // the lineage count's normal is the sine partner of Z_E's
+            // Box-Muller pair) or the geodesic Gaussian step of per-axis
+            // variance t.
+            if (flags & kMcs) {
+                R sig2;
+                if constexpr (M::f64) {
+                    sig2 = ld_time64(P.mats64[mat], S, rho, E);
+                } else {
+                    const float A1 = fmaf(lf, tb.x - ta.x, ta.x);
+                    const float A2 = fmaf(lf, tb.y - ta.y, ta.y);
+                    const float nu = rho * A2;
+                    const float br = (1.0f + M::rcp(nu)) * M::lg(1.0f + nu) - 1.0f;
+                    sig2 = rho * A1 * br;
                 }
-            } else {
-                polar_cs(R(-2) * sig2 * M::lg(u_hi<R>(w.z)), ct, st);
+                R ct = R(1), st = R(0);
+                if (flags & kSbm) {
+                    if (sig2 < SbmSwitch<R>::t) {
+                        const R zM = M::sq(R(-2) * M::lg(u_hi<R>(w.x))) * M::sinr(u_hi<R>(w.y));
+                        sbm_small(sig2, zM, u_hi<R>(w.z), ct, st);
+                        const R ph = u_hi<R>(w.w);
+                        turn(ox, oy, oz, ct, st, M::cosr(ph), M::sinr(ph));
+                    } else {   // exact regime: drawn at the top of the loop
+                        state = kTurn;
+                        sbm_pend = true;
+                        sbm_t = sig2;
+                        sbm_u = u_hi<R>(w.z);
+                        sbm_ph = u_hi<R>(w.w);
+                    }
+                } else {
+                    polar_cs(R(-2) * sig2 * M::lg(u_hi<R>(w.z)), ct, st);
+                    const R ph = u_hi<R>(w.w);
+                    turn(ox, oy, oz, ct, st, M::cosr(ph), M::sinr(ph));
+                }
             }
-            if (now) {
-                const R ph = u_hi<R>(w.w);
-                turn(ox, oy, oz, ct, st, M::cosr(ph), M::sinr(ph));
+            // A jump (and the renormalisation after it) is finished in a batch.
+            if (jumped) {
+                ej = E;
+                matj = mat;
+                rhoj = rho;
+                nj = n;
+                state = kJump;
             }
-        }
-        l_steps++;
-        if (jumped) {
-            // the jump (and the renormalisation after it) is finished in a batch
-            ej = E;
-            matj = mat;
-            rhoj = rho;
-            nj = n;
-            E = Ep;
-            n++;
-            state = kJump;
-        } else {
-            const R inv = M::rsq(ox * ox + oy * oy + oz * oz);
+            const R xy =
+                kFixed == kMethodGeodesic ? M::fma(ox, ox, oy * oy) : M::fma(oy, oy, ox * ox);
+            const R inv = jumped ? R(1) : M::rsq(M::fma(oz, oz, xy));
             ox *= inv;
             oy *= inv;
             oz *= inv;
             E = Ep;
             n++;
             // Lane guard, folded into the exit test: a non-finite energy or
-            // direction (one non-finite component reaches all three through
-            // the renormalisation, and the move then leaves the box, so this
-            // step's deposit was scored as escaped) ends the history; its
-            // energy goes to the bad-lane ledger slot, so the energy balance
-            // still closes, and its record ends with code 6.
+            // direction (one non-finite component reaches all three through the
+            // renormalisation, and the move then leaves the box, so this step's
+            // deposit was scored as escaped) ends the history; its energy goes to
+            // the bad-lane ledger slot, so the energy balance still closes, and
+            // its record ends with code 6.
             const bool bad = !__builtin_isfinite(E * ox);
-            if (!in_next || bad) {
-                if (bad) {
-                    l_bad += __builtin_isfinite(E) ? fixp(E, wsc) : 0ll;
-                    record(P, h, (float)e0, n, hj, 6, (float)rx, (float)ry, (float)rz, (float)E,
-                           j1, j2);
+            if (!jumped && (!in_next || bad || E < S.e_min)) {
+                if (!in_next || bad) {
+                    if (bad) {
+                        l_bad += __builtin_isfinite(E) ? fixp(E, wsc) : 0ll;
+                        record<kRec>(P, h, (float)e0, n, hj, 6, (float)rx, (float)ry, (float)rz,
+                                     (float)E, j1, j2);
+                    } else {
+                        l_esc += fixp(E, wsc);
+                        record<kRec>(P, h, (float)e0, n, hj, 2, (float)rx, (float)ry, (float)rz,
+                                     (float)E, j1, j2);
+                    }
                 } else {
-                    l_esc += fixp(E, wsc);
-                    record(P, h, (float)e0, n, hj, 2, (float)rx, (float)ry, (float)rz, (float)E,
-                           j1, j2);
+                    score(P, S, tile, rep, acc, rx, ry, rz, E, wsc, l_esc);
+                    record<kRec>(P, h, (float)e0, n, hj, 3, (float)rx, (float)ry, (float)rz, (float)E,
+                                 j1, j2);
                 }
                 state = kDead;
-            } else if (E < S.e_min) {
-                score(P, S, tile, rep, acc, rx, ry, rz, E, wsc, l_esc);
-                record(P, h, (float)e0, n, hj, 3, (float)rx, (float)ry, (float)rz, (float)E, j1,
-                       j2);
-                state = kDead;
             }
-        }
-        if (in_next && v_next != vcache) {
-            rho = (R)__uint_as_float(pk_next.x);
-            mat = (int)pk_next.y;
-            vcache = v_next;
+            if (v_next != vcache) {
+                rho = (R)__uint_as_float(pk_next.x);
+                mat = (int)pk_next.y;
+                vcache = v_next;
+                mc = matc[mat];
+            }
         }
     }
 
+    l_steps += n;
     acc_flush(tile, rep, acc);
-    // ledger: wave sums, one atomic per slot per wave
+    // ledger: wave sums, added up in LDS (where the tables were), then one
+    // atomic per slot and workgroup, all slots in one instruction; one per slot
+    // and wave, idle waves included, was 290 us of 4096 waves on one line
     const unsigned long long s_esc = wave_sum((unsigned long long)l_esc);
     const unsigned long long s_nuc = wave_sum((unsigned long long)l_nuc);
     const unsigned long long s_e0 = wave_sum((unsigned long long)l_e0);
@@ -1390,18 +1445,27 @@ __global__ void __launch_bounds__(1024) k_transport(KParams P) {
     const unsigned long long s_hi = wave_sum((unsigned long long)l_hist);
     const unsigned long long s_ju = wave_sum((unsigned long long)l_jumps);
     const unsigned long long s_bad = wave_sum((unsigned long long)l_bad);
-    if (lane == 0) {
-        if (s_bad) atomicAdd(&P.ledger[8], s_bad);
-        atomicAdd(&P.ledger[1], s_esc);
-        atomicAdd(&P.ledger[2], s_nuc);
-        atomicAdd(&P.ledger[3], s_e0);
-        atomicAdd(&P.ledger[5], s_st);
-        atomicAdd(&P.ledger[6], s_hi);
-        atomicAdd(&P.ledger[7], s_ju);
-    }
-
-    // flush the LDS tile
+    __syncthreads();   // no wave reads the tables any more
+    unsigned long long* red = reinterpret_cast<unsigned long long*>(smem);
+    if (threadIdx.x < kLedgerN) red[threadIdx.x] = 0ull;
     __syncthreads();
+    if (lane == 0 && s_hi) {
+        auto add = [&](int slot, unsigned long long v) {
+            __hip_atomic_fetch_add(&red[slot], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        };
+        add(1, s_esc);
+        add(2, s_nuc);
+        add(3, s_e0);
+        add(5, s_st);
+        add(6, s_hi);
+        add(7, s_ju);
+        add(8, s_bad);
+    }
+    __syncthreads();
+    if (threadIdx.x < kLedgerN && red[threadIdx.x])
+        atomicAdd(&P.ledger[threadIdx.x], red[threadIdx.x]);
+
+    // flush the LDS tile (complete since the barriers above)
     for (int i = threadIdx.x; i < tile_n; i += blockDim.x) {
         const unsigned long long q = tile[i];
         if (q) {
@@ -1582,11 +1646,13 @@ hipError_t launch_reset(unsigned long long* tally, size_t nvox, unsigned long lo
 }
 
 hipError_t transport_kernel_attributes(size_t lds_bytes) {
-    const void* fns[] = {reinterpret_cast<const void*>(&k_transport<float, kMethod, false>),
-                         reinterpret_cast<const void*>(&k_transport<float, kMethodGeodesic, false>),
-                         reinterpret_cast<const void*>(&k_transport<float, 0u, false>),
-                         reinterpret_cast<const void*>(&k_transport<float, 0u, true>),
-                         reinterpret_cast<const void*>(&k_transport<double, 0u, true>)};
+    const void* fns[] = {reinterpret_cast<const void*>(&k_transport<float, kMethod, false, false>),
+                         reinterpret_cast<const void*>(&k_transport<float, kMethod, false, true>),
+                         reinterpret_cast<const void*>(&k_transport<float, kMethodGeodesic, false, false>),
+                         reinterpret_cast<const void*>(&k_transport<float, kMethodGeodesic, false, true>),
+                         reinterpret_cast<const void*>(&k_transport<float, 0u, false, true>),
+                         reinterpret_cast<const void*>(&k_transport<float, 0u, true, true>),
+                         reinterpret_cast<const void*>(&k_transport<double, 0u, true, true>)};
     for (const void* f : fns) {
         const hipError_t e =
             hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
@@ -1597,21 +1663,22 @@ hipError_t transport_kernel_attributes(size_t lds_bytes) {
 
 hipError_t launch_transport(const KParams& p, int grid, int block, size_t lds_bytes,
                             hipStream_t s) {
+    const bool rec = p.rec != nullptr;
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(block), lds_bytes, s, p);
+    };
     if (p.fp64)
-        hipLaunchKernelGGL((k_transport<double, 0u, true>), dim3(grid), dim3(block), lds_bytes, s,
-                           p);
+        go(k_transport<double, 0u, true, true>);
     else if (p.n_ni > 0 || p.n_l > 0)   // elastic nuclear data
-        hipLaunchKernelGGL((k_transport<float, 0u, true>), dim3(grid), dim3(block), lds_bytes, s,
-                           p);
+        go(k_transport<float, 0u, true, true>);
     else if (p.flags == kMethod)
-        hipLaunchKernelGGL((k_transport<float, kMethod, false>), dim3(grid), dim3(block),
-                           lds_bytes, s, p);
+        rec ? go(k_transport<float, kMethod, false, true>)
+            : go(k_transport<float, kMethod, false, false>);
     else if (p.flags == kMethodGeodesic)
-        hipLaunchKernelGGL((k_transport<float, kMethodGeodesic, false>), dim3(grid), dim3(block),
-                           lds_bytes, s, p);
+        rec ? go(k_transport<float, kMethodGeodesic, false, true>)
+            : go(k_transport<float, kMethodGeodesic, false, false>);
     else
-        hipLaunchKernelGGL((k_transport<float, 0u, false>), dim3(grid), dim3(block), lds_bytes, s,
-                           p);
+        go(k_transport<float, 0u, false, true>);
     return hipGetLastError();
 }
 
