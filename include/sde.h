@@ -193,15 +193,17 @@ typedef struct {
     const float* density;           /* (device) [nz][ny][nx], g/cm^3, > 0 */
 } sde_phantom;
 
-/* Launch configuration; zero fields take defaults.  Results do not depend
- * on it. */
+/* Launch configuration; zero fields take the defaults in parentheses.
+ * Without one (a NULL launch) the library chooses from the beam, the phantom
+ * and the number of histories: the size of the launch, and a tile for a beam
+ * within 4 cm.  Results do not depend on it. */
 typedef struct {
     int block;        /* threads per workgroup, multiple of 64, <= 1024 (512) */
     int grid;         /* workgroups (0: 2 per compute unit) */
     int refill;       /* refill when at least this many lanes of a wave are idle, 1..64 (8) */
     int jump_batch;   /* finish deferred jumps when this many lanes of a wave wait, 1..64 (8) */
     int tally_replicas; /* global tally copies, chosen per XCD and summed at the end, 1..16 (8) */
-    int claim_chunk;  /* history indices a wave takes from the work counter at once, >= 64 (64) */
+    int claim_chunk;  /* most history indices a wave takes from the work counter at once, >= 64 (64) */
     int tile_nx, tile_ny, tile_nz;   /* LDS tally tile extent in voxels (0: none) */
     int tile_x0, tile_y0, tile_z0;   /* tile low corner in voxels */
     uint64_t nan_history;  /* test hook: 0 none; else history nan_history - 1 starts with a

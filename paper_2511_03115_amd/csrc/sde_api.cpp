@@ -175,6 +175,71 @@ int plan_enqueue(sde_plan* p, double* dose_out, hipStream_t s, bool timing = fal
     return SDE_OK;
 }
 
+// The launch of a caller who names none.
+//
+// Workgroups: one per CU with as many waves as the histories fill at one
+// per lane, 1 to 4 on each SIMD.  While no lane is ever refilled the launch
+// lasts as long as its longest history, so a wave's jumps and ends run without
+// waiting for others of their kind (1e4 histories of 100 MeV: 0.60 ms with the
+// batches of 8 that suit refilled lanes, 0.26 ms with 1; 2e5 at 150 MeV 1.33
+// and 1.13 ms); up to four refills per lane the last histories still count
+// (1e6 on a patch of plan spots: 5.26 ms with 8, 5.07 with 4; 2e6: 6.58 and
+// 6.81).
+//
+// Tally tile: a beam within 4 cm scores most of its deposits in few voxel
+// columns, and atomics on those serialise (1e6 histories of 150 MeV at 1 mm:
+// 9.0 ms without a tile, 4.2 ms with one of 10 x 10 columns; 6.1 and 6.5 ms
+// with 6 or 16 columns a side, which leave out the flanks or the end of the
+// range).  It is the widest of 12, 10, 8 and 6 columns a side that three
+// quarters of the beam's depth still fit.
+sde_launch default_launch(const sde_beam* beam, const sde_phantom* ph,
+                          const std::vector<uint64_t>& counts, uint64_t total, int n_cu,
+                          size_t tile_budget) {
+    sde_launch L{};
+    const uint64_t lanes = 256ull * (uint64_t)std::max(1, n_cu);   // one wave per SIMD
+    const uint64_t per = std::min<uint64_t>((total + lanes - 1) / lanes, 4);
+    L.block = (int)(256 * std::max<uint64_t>(per, 1));
+    L.grid = std::max(1, n_cu);
+    L.refill = 4;
+    L.jump_batch = total <= 4 * lanes ? 1 : total <= 16 * lanes ? 4 : 8;
+    double lo[2] = {1e300, 1e300}, hi[2] = {-1e300, -1e300}, c[2] = {0, 0};
+    double sigma = 0, emax = 0, wsum = 0;
+    for (int i = 0; i < beam->n_spots; ++i) {
+        if (!counts[i]) continue;
+        const sde_spot& s = beam->spots[i];
+        const double x[2] = {s.x_cm, s.y_cm};
+        for (int a = 0; a < 2; ++a) {
+            lo[a] = std::min(lo[a], x[a]);
+            hi[a] = std::max(hi[a], x[a]);
+            c[a] += s.weight * x[a];
+        }
+        sigma = std::max(sigma, s.sigma_xy_cm);
+        emax = std::max(emax, s.E_MeV);
+        wsum += s.weight;
+    }
+    if (!(std::max(hi[0] - lo[0], hi[1] - lo[1]) + 6 * sigma < 4.0) || !(wsum > 0)) return L;
+    // depth of the highest energy in water (Bragg-Kleeman), with a margin
+    const double deep = std::ceil(0.0022 * std::pow(emax, 1.77) * 1.15 / ph->dz_cm) + 2;
+    const int depth = (int)std::min<double>(deep, ph->nz);
+    const double d[2] = {ph->dx_cm, ph->dy_cm};
+    const int n[2] = {ph->nx, ph->ny};
+    for (const int t : {12, 10, 8, 6}) {
+        const int fit = (int)std::min<size_t>((size_t)depth, tile_budget / (8 * (size_t)t * t));
+        if (t > n[0] || t > n[1] || fit < 8 || 4 * fit < 3 * depth) continue;
+        int x0[2];
+        for (int a = 0; a < 2; ++a) {
+            const double v = std::floor((c[a] / wsum - ph->origin_cm[a]) / d[a]) - t / 2;
+            x0[a] = (int)std::min(std::max(v, 0.0), (double)(n[a] - t));
+        }
+        L.tile_nx = L.tile_ny = t;
+        L.tile_nz = fit;
+        L.tile_x0 = x0[0];
+        L.tile_y0 = x0[1];
+        break;
+    }
+    return L;
+}
+
 int make_plan(const sde_beam* beam, const sde_phantom* ph, uint64_t n_histories, uint64_t seed,
               const sde_launch* launch, sde_plan** out) {
     if (!g.ready) return fail(SDE_E_STATE, "sde_init_materials has not been called");
@@ -226,8 +291,11 @@ int make_plan(const sde_beam* beam, const sde_phantom* ph, uint64_t n_histories,
     if (k < -60 || k > 100) return fail(SDE_E_OVERFLOW, "fixed-point scale out of range");
     const double scale = std::ldexp(1.0, k);
 
-    sde_launch L{};
-    if (launch) L = *launch;
+    const size_t tab_bytes = ((size_t)T.n_mat * T.n_e + T.n_mat) * sizeof(float4);
+    const sde_launch L =
+        launch ? *launch
+               : default_launch(beam, ph, counts, total, g.n_cu,
+                                g.max_lds > tab_bytes ? g.max_lds - tab_bytes : 0);
     const int n_rep = L.tally_replicas ? L.tally_replicas : 8;
     if (n_rep < 1 || n_rep > 16) return fail(SDE_E_INVALID, "tally_replicas must be in 1..16");
 
@@ -331,7 +399,6 @@ int make_plan(const sde_beam* beam, const sde_phantom* ph, uint64_t n_histories,
         plan_free(p);
         return fail(SDE_E_INVALID, "LDS tile outside the phantom");
     }
-    const size_t tab_bytes = ((size_t)T.n_mat * T.n_e + T.n_mat) * sizeof(float4);
     const size_t tile_bytes = tile_on ? (size_t)tnx * tny * tnz * 8 : 0;
     if (tab_bytes + tile_bytes > g.max_lds) {
         plan_free(p);
