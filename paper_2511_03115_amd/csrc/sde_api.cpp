@@ -129,6 +129,7 @@ struct sde_plan {
     int n_rep = 1;
     double scale = 1.0;
     double voxel_cm3 = 0;
+    bool dirty = false;   // an execution failed half-way: every reset clears all replicas
     hipGraph_t graph = nullptr;
     hipGraphExec_t gexec = nullptr;
     double* graph_dose = nullptr;
@@ -158,8 +159,17 @@ void plan_free(sde_plan* p) {
 
 // Enqueue reset, transport and the replica sum / dose conversion on stream s
 // (dose_out may be NULL); with timing, HIP events bracket the transport launch.
-int plan_enqueue(sde_plan* p, double* dose_out, hipStream_t s, bool timing = false) {
-    HIP_TRY(launch_reset(p->tally, p->nvox * p->n_rep, p->ledger, p->counter, s));
+// Replicas 1.. are zero between executions (zeroed when the plan is made, left
+// so by the conversion), so the reset clears replica 0 alone: 64 -> 8 B per
+// voxel, 121 -> 20 us on 12M voxels.  cleared: nothing has run since the plan
+// was made, and the reset is left out.
+int plan_enqueue(sde_plan* p, double* dose_out, hipStream_t s, bool timing = false,
+                 bool cleared = false) {
+    if (!cleared)
+        HIP_TRY(launch_reset(p->tally, p->dirty ? p->nvox * p->n_rep : p->nvox, p->ledger,
+                             p->counter, s));
+    const bool dirty = p->dirty;
+    p->dirty = true;   // until the conversion is enqueued
     if (timing) {
         if (!p->ev0) HIP_TRY(hipEventCreate(&p->ev0));
         if (!p->ev1) HIP_TRY(hipEventCreate(&p->ev1));
@@ -172,6 +182,7 @@ int plan_enqueue(sde_plan* p, double* dose_out, hipStream_t s, bool timing = fal
     }
     HIP_TRY(launch_convert(p->tally, p->n_rep, p->vox, p->nvox, 1.0 / p->scale, p->voxel_cm3,
                            dose_out, p->ledger, s));
+    p->dirty = dirty;
     return SDE_OK;
 }
 
@@ -296,7 +307,17 @@ int make_plan(const sde_beam* beam, const sde_phantom* ph, uint64_t n_histories,
         launch ? *launch
                : default_launch(beam, ph, counts, total, g.n_cu,
                                 g.max_lds > tab_bytes ? g.max_lds - tab_bytes : 0);
-    const int n_rep = L.tally_replicas ? L.tally_replicas : 8;
+    // Replicas keep hot lines in one XCD's L2, but each costs a pass over the
+    // voxels to sum.  With at most one history per lane two do (2e5 on 8M
+    // voxels: 1.23 ms with 2, 1.20 with 4, 1.28 with 8; 1e5 on 2M: kernel 0.91
+    // with any); to 65536 per compute unit four (1e6 on 8M: 4.72, 4.42 and 4.39;
+    // 1e6 on 12M: 4.16, 4.28 and 4.37; 2e6 on 13M: 6.76, 6.78 and 6.90);
+    // beyond, the atomics decide (2e7 on 13M: 66.4, 65.3 and 65.0).
+    const uint64_t per_cu = total / (uint64_t)std::max(1, g.n_cu);
+    const int n_rep = L.tally_replicas ? L.tally_replicas
+                      : per_cu <= 1024 ? 2
+                      : per_cu <= 65536 ? 4
+                                        : 8;
     if (n_rep < 1 || n_rep > 16) return fail(SDE_E_INVALID, "tally_replicas must be in 1..16");
 
     sde_plan* p = new sde_plan();
@@ -348,6 +369,7 @@ int make_plan(const sde_beam* beam, const sde_phantom* ph, uint64_t n_histories,
     }
     hipStream_t s = cur_stream();
     if ((e = hipMemsetAsync(p->bad, 0, sizeof(unsigned int) * (1 + kMaxMat), s)) != hipSuccess ||
+        (e = launch_reset(p->tally, nvox * n_rep, p->ledger, p->counter, s)) != hipSuccess ||
         (e = launch_pack_phantom(ph->material_id, ph->density, p->vox, nvox, T.n_mat, p->bad,
                                  p->bad + 1, s)) != hipSuccess) {
         plan_free(p);
@@ -680,7 +702,7 @@ int sde_plan_execute(sde_plan* p, double* dose_out, int use_graph) {
         if (!g.own) HIP_TRY(hipStreamCreate(&g.own));
         s = g.own;
     }
-    if (!p->gexec || p->graph_dose != dose_out || p->graph_stream != s) {
+    if (!p->gexec || p->dirty || p->graph_dose != dose_out || p->graph_stream != s) {
         if (p->gexec) (void)hipGraphExecDestroy(p->gexec);
         if (p->graph) (void)hipGraphDestroy(p->graph);
         p->gexec = nullptr;
@@ -757,7 +779,7 @@ int sde_transport_ex(const sde_beam* beam, const sde_phantom* phantom, uint64_t 
     int rc = make_plan(beam, phantom, n_histories, seed, launch, &p);
     if (rc != SDE_OK) return rc;
     hipStream_t s = cur_stream();
-    rc = plan_enqueue(p, dose_out, s);
+    rc = plan_enqueue(p, dose_out, s, false, true);
     if (rc == SDE_OK && tally_out) {
         const hipError_t e = hipMemcpyAsync(tally_out, p->tally, sizeof(int64_t) * p->nvox,
                                             hipMemcpyDeviceToDevice, s);
