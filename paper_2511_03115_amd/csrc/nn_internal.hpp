@@ -80,10 +80,10 @@ hipError_t flip_transpose_all(const FlipJobs& jobs, hipStream_t s);
 hipError_t flip_transpose(const uint16_t* w, uint16_t* wt, int Ci, int Co, hipStream_t s);
 // weight gradient: part needs wgrad_part_floats floats; dw [Co][27][Ci], db [Co]
 // (nullable).  Ci % 16 == 0, Co % 16 == 0, (Co/16)(Ci/16) <= 64, chunk from
-// wgrad_chunk_for (a multiple of 64).  16, 32, 64 or 128 outputs go by
-// 4 x 4 x 16 bricks (at most as many split-K chunks as the chunk length
-// gives; 64 and 128 as groups of 32), other widths by 64-voxel slices and
-// tap groups.
+// wgrad_chunk_for (a multiple of 64).  By 16 x 8 voxel columns along z, or by
+// 4 x 4 x 16 bricks (the smallest layers with 16 or 32 outputs), with at most as
+// many split-K chunks as the chunk length gives; operands of 2 GiB and more by
+// 64-voxel slices and tap groups.
 long long wgrad_chunks(const int* dims, int chunk);
 int wgrad_chunk_for(const int* dims, int Ci, int Co, long long max_part_floats);
 long long wgrad_part_floats(const int* dims, int Ci, int Co, int chunk);
@@ -91,7 +91,7 @@ hipError_t wgrad(const uint16_t* dz, const uint16_t* x, const int* dims, int Ci,
                  float* part, float* dw, float* db, hipStream_t s);
 // wgrad of a conv whose input is the decoder's concatenation [skip (Cs
 // channels), nearest-upsampled low (Cu channels, half-size level)], read in
-// place.  Supported (by bricks) when wgrad_cat_supported says so; the part
+// place.  Supported when wgrad_cat_supported says so; the part
 // buffer is sized as for wgrad with Ci = Cs + Cu.
 bool wgrad_cat_supported(int Cs, int Cu, int Co, const int* dims);
 hipError_t wgrad_cat(const uint16_t* dz, const uint16_t* skip, const uint16_t* low,

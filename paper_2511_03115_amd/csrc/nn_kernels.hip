@@ -12,6 +12,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "nn_internal.hpp"
 
@@ -1486,7 +1487,8 @@ __global__ void k_flip_transpose(const uint16_t* w, uint16_t* wt, int Ci, int Co
 }
 
 // ---------------------------------------------------------------------------
-// Weight and bias gradients, split over voxel chunks:
+// Weight and bias gradients where an operand has 2 GiB or more, split over
+// voxel chunks:
 //   part[c][t][co][ci] = sum_{v in chunk c} dz[v][co] x[shift(v, t)][ci],
 //   part_b[c][co]      = sum_{v in chunk c} dz[v][co].
 // Workgroup = (chunk, group of tg taps).  64-voxel slices of dz and of the
@@ -1649,8 +1651,8 @@ __global__ void __launch_bounds__(256) k_wgrad_partial(const uint16_t* __restric
 }
 
 // ---------------------------------------------------------------------------
-// Weight and bias gradients of the layers with 16 or 32 outputs, by bricks:
-// the same partial sums part[c][t][co][ci] as k_wgrad_partial, with chunk c
+// Weight and bias gradients of the smallest layers with 16 or 32 outputs, by
+// bricks: the same partial sums part[c][t][co][ci] as k_wgrad_partial, with chunk c
 // a run of 4 x 4 x 16 voxel bricks (the bricks of k_conv_fwd_reg) and one
 // workgroup per (chunk, 16 input channels).  Per brick the dz values are
 // staged transposed in LDS ([co][voxel]) and the input brick with its halo
@@ -1680,8 +1682,7 @@ k_wgrad_brick(const uint16_t* __restrict__ dz,
                                                      const uint16_t* __restrict__ xl, Geo g, int Ci,
                                                      int Cs, int bpc, int nbk,
                                                      float* __restrict__ part,
-                                                     float* __restrict__ part_b, int dzc) {
-    // dz: Co = 16 NCO output channels of dzc per voxel (a group of a wider layer).
+                                                     float* __restrict__ part_b) {
     // Input channels [0, Cs) come from x (Cs per voxel), [Cs, Ci) from the
     // half-size level xl, nearest-neighbour upsampled (the decoder's
     // concatenation read in place; Cs = Ci for a plain input).
@@ -1712,7 +1713,7 @@ k_wgrad_brick(const uint16_t* __restrict__ dz,
     // buffer loads (32-bit offsets; the host keeps both operands below 2 GiB):
     // a voxel outside the volume is read at an offset past the end, which
     // the hardware answers with zeros, so no load sits behind a branch
-    const __amdgpu_buffer_rsrc_t dzr = rsrc16(dz, g.nvox() * dzc);
+    const __amdgpu_buffer_rsrc_t dzr = rsrc16(dz, g.nvox() * Co);
     // this workgroup's 16 input channels come from one source (Cs is a
     // multiple of 16)
     const bool lowsrc = ci0 >= Cs;
@@ -1732,11 +1733,11 @@ k_wgrad_brick(const uint16_t* __restrict__ dz,
             const int vg = i / (Co / 8), ch = (i % (Co / 8)) * 8;
             const int rr = vg >> 1, zz = z0 + (rr >> 2), yy = y0 + (rr & 3), xs = x0 + (vg & 1) * 8;
             const bool rin = i < NDZ && zz < g.D && yy < g.H;
-            const int o = ((((b * g.D + zz) * g.H + yy) * g.W + xs) * dzc + ch) * 2;
+            const int o = ((((b * g.D + zz) * g.H + yy) * g.W + xs) * Co + ch) * 2;
 #pragma unroll
             for (int k = 0; k < 8; ++k)
                 rdz[k] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(
-                                                       dzr, rin && xs + k < g.W ? o + k * dzc * 2 : kOob,
+                                                       dzr, rin && xs + k < g.W ? o + k * Co * 2 : kOob,
                                                        0, 0));
         }
         {
@@ -1843,69 +1844,332 @@ k_wgrad_brick(const uint16_t* __restrict__ dz,
     }
 }
 
-// dW[co][t][ci] = sum_c part[c][t][co][ci] (fixed order: deterministic).
+// ---------------------------------------------------------------------------
+// Weight and bias gradients by columns: the partial sums of 16 x 16 channel
+// blocks, over voxels.  A workgroup's halves (four waves each) march along z
+// over a pair of columns each, 16 voxels in x by 4 R in y and n planes long
+// (neighbours where the volume is wide, otherwise any two: they only share the
+// sum); a K-step is 16 voxels of one row of either column, in whatever order
+// the transposing loads give them, the same for both operands.
+//
+// What bounds it: memory, 64 B per voxel of a 16 -> 16 layer (26 us for 2.1M
+// voxels; 12 us of matrix cores); with more channels the matrix cores.
+// k_wgrad_brick stages three transposed copies of the input per brick and reads
+// a fragment from LDS for every product: it is bound by LDS (2500 clocks per
+// brick of 256 voxels, for 864 clocks of matrix cores) and by the latency
+// between its two barriers.  Here planes are staged as they lie in memory, 32 B
+// per voxel, and read with the transposing LDS load (a 16-voxel row is 512
+// consecutive bytes: no bank conflicts), so a shift along x is an offset of
+// 32 B; each wave owns R rows of the plane and all 27 taps (108 accumulator
+// registers), keeps the output gradients of three planes in registers, and
+// so uses each input fragment for up to 9 products.  Two planes' loads are
+// in flight during a plane's products (LDS double buffer, one barrier per
+// plane).  Eight waves per workgroup, one workgroup per CU: half the partial
+// sums of two workgroups of four (14 MB, 7 us to write and sum).  R = 4
+// needs more registers than two waves per SIMD have; leaving out the
+// products with the planes beyond a column's ends (2 / n of them) made the
+// allocator spill and took twice the time.
+// With the column sums, bricks -> columns: 4 x 128 x 64 x 64 voxels, 16 -> 16
+// channels 85 -> 40 us (3.4 TB/s), 48 -> 16 212 -> 100; 100 x 128 x 128,
+// 32 -> 32 149 -> 87 (1.04 PFLOP/s); 4 x 16 x 8 x 8, 128 -> 128 68 -> 22.
+// ---------------------------------------------------------------------------
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+
+constexpr int wgrad_cols_x_items(int R) { return 2 * (4 * R + 2) * 18 * 2; }   // 16 bytes each
+constexpr int wgrad_cols_d_items(int R) { return 256 * R; }
+constexpr int wgrad_cols_lds_bytes(int R) {
+    return 2 * 2 * 16 * (wgrad_cols_x_items(R) + wgrad_cols_d_items(R));
+}
+
+template <int R>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2)))
+k_wgrad_cols(const uint16_t* __restrict__ dz, const uint16_t* __restrict__ x,
+             const uint16_t* __restrict__ xl, Geo g, int Ci, int Cs, int Co, int n, int ncol,
+             int cpw, int used, float* __restrict__ part, float* __restrict__ part_b) {
+    // columns: x fastest, then y, z chunk, batch; half h of workgroup c takes
+    // the pairs [(2 c + h) cpw, (2 c + h + 1) cpw); a column past the last reads
+    // zeros
+    constexpr int RY = 4 * R, HY = RY + 2, NXI = wgrad_cols_x_items(R), NDI = wgrad_cols_d_items(R);
+    constexpr int NXL = (NXI + 255) / 256, NDL = NDI / 256;
+    extern __shared__ __align__(16) uint16_t lds_all[];   // [half][2][x items, dz items]
+    constexpr int BUF = (NXI + NDI) * 8;                   // elements of one buffer
+    const int tid = threadIdx.x & 255, lane = tid & 63, wave = tid >> 6;   // of this half
+    const int half_id = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
+    uint16_t* const lds = lds_all + half_id * 2 * BUF;
+    // workgroups go round the 8 XCDs in turn (the grid is a multiple of 8): an
+    // XCD takes neighbouring columns, all channel blocks of one after the
+    // other, so that what they share meets in its L2
+    const int wi = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    const int nci = Ci / 16, nblk = nci * (Co / 16);
+    const int c = wi / nblk, cib = wi % nblk % nci, cob = wi % nblk / nci;
+    const int ci0 = cib * 16, co0 = cob * 16;
+    if (c >= used) return;
+    const int nbx = (g.W + 15) / 16, nby = (g.H + RY - 1) / RY, nbz = (g.D + n - 1) / n;
+    const int p0 = (2 * c + half_id) * cpw, steps = cpw * (n + 2);
+    const bool lowsrc = ci0 >= Cs;
+    const int Cu = Ci - Cs, Dd = g.D >> 1;
+    const __amdgpu_buffer_rsrc_t dzr = rsrc16(dz, g.nvox() * Co);
+    const __amdgpu_buffer_rsrc_t xr =
+        lowsrc ? rsrc16(xl, g.nvox() / 8 * Cu) : rsrc16(x, g.nvox() * Cs);
+    const int low = lowsrc, xcs = (lowsrc ? Cu : Cs) * 2;
+    const int xplane = (g.H >> low) * (g.W >> low) * xcs, dplane = g.H * g.W * Co * 2;
+    const int xc = (lowsrc ? ci0 - Cs : ci0) * 2;
+
+    // staging: the pair's columns and, of every item this thread loads, the
+    // byte offset within a plane (kOob outside the volume)
+    int sz0[2];
+    int xo[NXL], dof[NDL];
+    auto pick = [](int s, int u, int v) { return u ^ ((u ^ v) & -s); };   // s ? v : u, branch-free
+    auto set_pair = [&](int p) {
+        int t0 = tid;
+        asm("" : "+v"(t0));   // the items' places are recomputed, not kept in registers
+        int x0[2], y0[2], bx[2], bd[2];
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            int r = 2 * p + s;
+            const bool in = r < ncol;
+            x0[s] = in ? (r % nbx) * 16 : g.W + 16;
+            r /= nbx;
+            y0[s] = (r % nby) * RY;
+            r /= nby;
+            sz0[s] = (r % nbz) * n;
+            const int b = in ? r / nbz : 0;
+            bx[s] = b * (lowsrc ? Dd : g.D) * xplane + xc;
+            bd[s] = b * g.D * dplane + co0 * 2;
+        }
+#pragma unroll
+        for (int k = 0; k < NXL; ++k) {
+            const int i = t0 + 256 * k;
+            const int half = i & 1, v = (i >> 1) % 18, row = (i / 36) % HY, s = i >= 36 * HY;
+            const int xx = pick(s, x0[0], x0[1]) - 1 + v, yy = pick(s, y0[0], y0[1]) - 1 + row;
+            const int o = ((yy >> low) * (g.W >> low) + (xx >> low)) * xcs + half * 16;
+            xo[k] = (unsigned)xx < (unsigned)g.W && (unsigned)yy < (unsigned)g.H && i < NXI
+                        ? pick(s, bx[0], bx[1]) + o
+                        : kOob;
+        }
+#pragma unroll
+        for (int k = 0; k < NDL; ++k) {
+            const int i = t0 + 256 * k, s = k / (NDL / 2);
+            const int half = i & 1, v = (i >> 1) & 15, row = (i >> 5) % RY;
+            const int xx = x0[s] + v, yy = y0[s] + row;
+            dof[k] = xx < g.W && yy < g.H ? bd[s] + (yy * g.W + xx) * Co * 2 + half * 16 : kOob;
+        }
+    };
+    uint4 rx[2][NXL], rd[2][NDL];   // two steps' planes in flight
+    int lk = 0, lp = p0;            // the step whose planes are loaded next
+    auto load_raw = [&](auto set) {
+        constexpr int S = decltype(set)::value;
+        if (lk == 0) set_pair(lp);
+        int xz[2], zz[2];
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const int z = sz0[s] - 1 + lk;   // input plane; output gradients of plane z + 1
+            xz[s] = z >= 0 && z < g.D ? (z >> low) * xplane : kOob;
+            zz[s] = lk < n && z + 1 < g.D ? (z + 1) * dplane : kOob;
+        }
+#pragma unroll
+        for (int k = 0; k < NXL; ++k)
+            rx[S][k] = __builtin_bit_cast(
+                uint4, __builtin_amdgcn_raw_buffer_load_b128(
+                           xr, (int)((unsigned)xo[k] +
+                                     (unsigned)pick(tid + 256 * k >= 36 * HY, xz[0], xz[1])),
+                           0, 0));
+#pragma unroll
+        for (int k = 0; k < NDL; ++k)
+            rd[S][k] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(
+                                                  dzr, (int)((unsigned)dof[k] + (unsigned)zz[k / (NDL / 2)]),
+                                                  0, 0));
+        if (++lk == n + 2) {
+            lk = 0;
+            ++lp;
+        }
+    };
+    auto store_lds = [&](auto set) {
+        constexpr int S = decltype(set)::value;
+        uint4* d = reinterpret_cast<uint4*>(lds + S * BUF);
+#pragma unroll
+        for (int k = 0; k < NXL; ++k)
+            if (tid + 256 * k < NXI) d[tid + 256 * k] = rx[S][k];
+#pragma unroll
+        for (int k = 0; k < NDL; ++k) d[NXI + tid + 256 * k] = rd[S][k];
+    };
+    // 16 voxels x 16 channels at element offset o: lane l gets channel l % 16
+    // of voxels 4 (l / 16) + [0, 4)
+    auto frag = [&](int o0, int o1) {
+        union {
+            s16x4 h[2];
+            bf16x8 v;
+        } u;
+        u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(lds + o0));
+        u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(lds + o1));
+        return u.v;
+    };
+
+    f32x4 acc[27], accb = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < 27; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    bf16x8 a[3][R];   // output gradients of planes z + 1, z, z - 1
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+#pragma unroll
+        for (int r = 0; r < R; ++r) a[q][r] = as_bf16x8(make_uint4(0, 0, 0, 0));
+    const bf16x8 ones = as_bf16x8(make_uint4(0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u));
+
+    // the products of one input plane
+    auto products = [&](int base) {
+#pragma unroll
+        for (int hr = 0; hr < R + 2; ++hr)
+#pragma unroll
+            for (int tx = 0; tx < 3; ++tx) {
+                const int o = base + (hr * 18 + tx) * 16;
+                const bf16x8 b = frag(o, o + HY * 18 * 16);
+#pragma unroll
+                for (int ty = 0; ty < 3; ++ty) {
+                    const int r = hr - ty;
+                    if (r < 0 || r >= R) continue;
+#pragma unroll
+                    for (int tz = 0; tz < 3; ++tz)
+                        acc[tz * 9 + ty * 3 + tx] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                            a[tz][r], b, acc[tz * 9 + ty * 3 + tx], 0, 0, 0);
+                }
+            }
+    };
+
+    const std::integral_constant<int, 0> even{};
+    const std::integral_constant<int, 1> odd{};
+    // step st from buffer b = st & 1; the next step's planes go to the other
+    // buffer, and the loads of the one after the next are in flight meanwhile
+    auto step = [&](int st, auto b, auto nb) {
+        __syncthreads();   // buffer b is written, the other one read
+        const int buf = decltype(b)::value * BUF;
+        const int xb = buf + wave * R * 18 * 16 + lane * 4;
+        const int db = buf + NXI * 8 + wave * R * 256 + lane * 4;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            a[2][r] = a[1][r];
+            a[1][r] = a[0][r];
+            a[0][r] = frag(db + r * 256, db + (RY + r) * 256);
+        }
+        if (cib == 0) {   // bias: products with ones
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                accb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0][r], ones, accb, 0, 0, 0);
+        }
+        products(xb);
+        if (st + 1 < steps) store_lds(nb);
+        if (st + 3 < steps) load_raw(nb);
+    };
+    load_raw(even);   // at least three steps
+    load_raw(odd);
+    store_lds(even);
+    load_raw(even);
+    for (int st = 0; st < steps; st += 2) {
+        step(st, even, odd);
+        if (st + 1 < steps) step(st + 1, odd, even);
+    }
+
+    // the eight waves' sums, nine taps at a time, in a fixed order
+    f32x4* const red = reinterpret_cast<f32x4*>(lds_all);   // [wave][9][64]
+    const int w8 = half_id * 4 + wave, t8 = threadIdx.x;
+    // part[co block][c][ci block][t][lane][4]: the accumulators as they lie
+    f32x4* const out = reinterpret_cast<f32x4*>(part) +
+                       (((size_t)cob * used + c) * nci + cib) * 27 * 64;
+#pragma unroll
+    for (int tz = 0; tz < 3; ++tz) {
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < 9; ++t) red[(w8 * 9 + t) * 64 + lane] = acc[tz * 9 + t];
+        __syncthreads();
+        for (int i = t8; i < 9 * 64; i += 512) {
+            f32x4 s = red[i];
+#pragma unroll
+            for (int w = 1; w < 8; ++w) s += red[w * 9 * 64 + i];
+            out[tz * 9 * 64 + i] = s;
+        }
+    }
+    if (cib == 0) {   // every column of the product with ones is the sum
+        __syncthreads();
+        if ((lane & 15) == 0) red[w8 * 4 + (lane >> 4)] = accb;
+        __syncthreads();
+        const float* rb = reinterpret_cast<const float*>(lds_all);
+        if (t8 < 16) {
+            float s = rb[t8];
+#pragma unroll
+            for (int w = 1; w < 8; ++w) s += rb[w * 16 + t8];
+            part_b[((size_t)cob * used + c) * 16 + t8] = s;
+        }
+    }
+}
+
 // Deterministic column sums out[c] = sum_r part[r * ncol + c]: a workgroup
 // of 64 x 16 threads owns 64 consecutive columns; row-group g sums rows
 // g, g + 16, ... (coalesced across the 64 columns) and the 16 partial sums
-// are added in a fixed order.  With ci_co > 0 the columns are the weight
-// gradient (t, co, ci) and are written to dW[co][t][ci] (ci_co = Ci * 65536 + Co).
+// are added in a fixed order.  One workgroup for the few columns there are:
+// bound by the latency of its rows' loads, eight in flight per thread.
 __global__ void __launch_bounds__(1024) k_colsum(const float* part, int nrow, int ncol,
-                                                 float* out, int ci_co) {
+                                                 float* out) {
     __shared__ float red[16][64];
     const int o = threadIdx.x & 63, gr = threadIdx.x >> 6;
     const int c = blockIdx.x * 64 + o;
     float s = 0.0f;
-    if (c < ncol)
+    if (c < ncol) {
+#pragma unroll 8
         for (int r = gr; r < nrow; r += 16) s += part[(size_t)r * ncol + c];
+    }
     red[gr][o] = s;
     __syncthreads();
     if (gr == 0 && c < ncol) {
         float t = 0.0f;
 #pragma unroll
         for (int k = 0; k < 16; ++k) t += red[k][o];
-        if (ci_co > 0) {
-            const int Ci = ci_co >> 16, Co = ci_co & 0xFFFF;
-            const int ci = c % Ci, co = (c / Ci) % Co, tap = c / (Ci * Co);
-            out[((size_t)co * 27 + tap) * Ci + ci] = t;
-        } else {
-            out[c] = t;
-        }
+        out[c] = t;
     }
 }
 
 // The weight and bias gradients' column sums in one launch: workgroups
 // [0, nbw) sum the weight partials (columns (t, co, ci), written to
 // dW[co][t][ci]), the rest the bias partials; each column in a fixed order.
-__global__ void __launch_bounds__(1024) k_colsum_wb(const float* part, const float* part_b,
-                                                    int nrow, int ncol, int nbw, int Co, float* dw,
-                                                    float* db, int ci_co) {
-    // a workgroup: 64 columns x 16 row groups (row group g sums rows g,
-    // g + 16, ...), the 16 partial sums then added in a fixed order.  The
-    // layer's Co outputs come in groups of cg = ci_co & 0xFFFF (each group's
-    // partials [row][t][co][ci] and bias partials [row][co] one after the
-    // other); column c < ncol = 27 Co Ci is (group, t, co, ci).
-    __shared__ float red[16][64];
+// Bound by the latency of a thread's row loads: 512 rows of 6912 columns with
+// one load in flight 11.6 us, 256 rows with eight 4.
+__global__ void __launch_bounds__(256) k_colsum_wb(const float* part, const float* part_b,
+                                                   int nrow, int ncol, int nbw, int Co, float* dw,
+                                                   float* db, int ci_co, int ngr, int frag) {
+    // a workgroup: 256 / ngr columns x ngr row groups (row group g sums rows
+    // g, g + ngr, ..., eight loads in flight), the ngr partial sums then added
+    // in a fixed order.  The layer's Co outputs come in groups of
+    // cg = ci_co & 0xFFFF (each group's partials [row][t][co][ci] and bias
+    // partials [row][co] one after the other); column c < ncol = 27 Co Ci is
+    // (group, t, co, ci).
+    __shared__ float red[256];
     const bool wpart = (int)blockIdx.x < nbw;
     const int Ci = ci_co >> 16, cg = ci_co & 0xFFFF;
-    const int o = threadIdx.x & 63, gr = threadIdx.x >> 6;
-    const int c = (wpart ? (int)blockIdx.x : (int)blockIdx.x - nbw) * 64 + o;
+    const int cpb = 256 / ngr, o = threadIdx.x % cpb, gr = threadIdx.x / cpb;
+    const int c = (wpart ? (int)blockIdx.x : (int)blockIdx.x - nbw) * cpb + o;
     const int nc = wpart ? ncol : Co;
     const int ng = 27 * cg * Ci;   // weight columns per group
     const int grp = wpart ? c / ng : c / cg, cc = wpart ? c - grp * ng : c - grp * cg;
     const float* src = wpart ? part + (size_t)grp * nrow * ng : part_b + (size_t)grp * nrow * cg;
     const int stride = wpart ? ng : cg;
     float s = 0.0f;
-    if (c < nc)
-        for (int r = gr; r < nrow; r += 16) s += src[(size_t)r * stride + cc];
-    red[gr][o] = s;
+    if (c < nc) {
+#pragma unroll 8
+        for (int r = gr; r < nrow; r += ngr) s += src[(size_t)r * stride + cc];
+    }
+    red[threadIdx.x] = s;
     __syncthreads();
     if (gr == 0 && c < nc) {
         float t = 0.0f;
-#pragma unroll
-        for (int k = 0; k < 16; ++k) t += red[k][o];
+        for (int k = 0; k < ngr; ++k) t += red[k * cpb + o];
         if (wpart) {
-            const int ci = cc % Ci, co = grp * cg + (cc / Ci) % cg, tap = cc / (Ci * cg);
-            dw[((size_t)co * 27 + tap) * Ci + ci] = t;
+            int ci = cc % Ci, co = (cc / Ci) % cg, tap = cc / (Ci * cg);
+            if (frag) {   // [ci block][t][lane][4]
+                const int l = (cc >> 2) & 63, k = cc >> 8;
+                tap = k % 27;
+                ci = k / 27 * 16 + (l & 15);
+                co = (l >> 4) * 4 + (cc & 3);
+            }
+            dw[((size_t)(grp * cg + co) * 27 + tap) * Ci + ci] = t;
         } else {
             db[c] = t;
         }
@@ -2645,9 +2909,52 @@ long long wgrad_part_floats(const int* dims, int Ci, int Co, int chunk) {
 }
 
 namespace {
+// 32-bit buffer offsets, and kOob past both operands
+bool wgrad_buffers(const Geo& g, int Ci, int Co) { return g.nvox() * std::max(Ci, Co) * 2 <= kOob; }
+
+// The smallest layers with 16 or 32 outputs go by bricks: columns have the
+// longer start and end (11.5k voxels, 32 -> 32 channels: bricks 14 us, columns
+// 16; 16.8k: 20 and 17; 16 -> 16 at 16.8k: 13 and 15, at 48k: 19 and 17).
 bool wgrad_by_bricks(const Geo& g, int Ci, int Co) {
-    return (Co == 16 || Co == 32 || Co == 64 || Co == 128) &&
-           g.nvox() * std::max(Ci, Co) * 2 < (1LL << 31);
+    return (Co == 16 || Co == 32) && g.nvox() * (Ci / 16) * (Co / 16) < 48000;
+}
+
+// The split of k_wgrad_cols: n planes per column, ncol columns, cpw pairs of
+// columns per half workgroup, used workgroups per channel block.
+constexpr int kWgColsR = 2;
+struct WgradCols {
+    int n, ncol, cpw, used;
+};
+WgradCols wgrad_cols_plan(const Geo& g, int Ci, int Co, long long max_used) {
+    const int RY = 4 * kWgColsR;
+    const long long nxy = (long long)((g.W + 15) / 16) * ((g.H + RY - 1) / RY) * g.B;
+    // one workgroup per CU in all, as far as the partial sums' buffer goes
+    const long long want =
+        std::max(1LL, std::min(max_used, 256LL / std::max(1, (Ci / 16) * (Co / 16))));
+    // the plane count whose longest workgroup marches over the fewest planes
+    // (of equals the longest columns)
+    WgradCols p{};
+    long long best = 1LL << 60;
+    for (int nz = 1; nz <= std::min(g.D, 64); ++nz) {
+        const int n = (g.D + nz - 1) / nz;
+        const long long ncol = nxy * ((g.D + n - 1) / n), pairs = (ncol + 1) / 2;
+        const long long cpw = (pairs + 2 * want - 1) / (2 * want);
+        if (ncol > (1 << 29) || cpw * (n + 2) >= best) continue;
+        best = cpw * (n + 2);
+        p = WgradCols{n, (int)ncol, (int)cpw, (int)((pairs + 2 * cpw - 1) / (2 * cpw))};
+    }
+    return p;
+}
+
+// dw and db (nullable) from nrow rows of partial sums, outputs in groups of cg
+hipError_t colsum_wb(const float* part, const float* part_b, int nrow, int Ci, int Co, int cg,
+                     float* dw, float* db, hipStream_t s, int frag = 0) {
+    // row groups: enough that a thread sums about 32 rows
+    const int ngr = nrow <= 32 ? 1 : nrow <= 64 ? 2 : nrow <= 128 ? 4 : nrow <= 256 ? 8 : 16;
+    const int n = 27 * Co * Ci, cpb = 256 / ngr, nbw = (n + cpb - 1) / cpb;
+    hipLaunchKernelGGL(k_colsum_wb, dim3(nbw + (db ? (Co + cpb - 1) / cpb : 0)), dim3(256), 0, s,
+                       part, part_b, nrow, n, nbw, Co, dw, db, (Ci << 16) | cg, ngr, frag);
+    return hipGetLastError();
 }
 
 // x: Cs channels per voxel; xl (the half-size level, Ci - Cs channels) when Cs < Ci
@@ -2656,21 +2963,36 @@ hipError_t wgrad_impl(const uint16_t* dz, const uint16_t* x, const uint16_t* xl,
                       hipStream_t s) {
     Geo g{dims[0], dims[1], dims[2], dims[3]};
     long long nchunk = wgrad_chunks(dims, chunk);
-    if (wgrad_by_bricks(g, Ci, Co)) {
-        // by bricks, within the same partial-sum buffer (32-bit buffer offsets);
-        // 64 or 128 outputs as groups of 32, each with its own partials
+    if (wgrad_buffers(g, Ci, Co)) {
         static const hipError_t attr = [] {
             hipError_t e = hipFuncSetAttribute((const void*)k_wgrad_brick<1>,
                                                hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024);
             if (e == hipSuccess)
                 e = hipFuncSetAttribute((const void*)k_wgrad_brick<2>,
                                         hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024);
+            if (e == hipSuccess)
+                e = hipFuncSetAttribute((const void*)k_wgrad_cols<kWgColsR>,
+                                        hipFuncAttributeMaxDynamicSharedMemorySize,
+                                        wgrad_cols_lds_bytes(kWgColsR));
             return e;
         }();
         if (attr != hipSuccess) return attr;
+    }
+    if (wgrad_buffers(g, Ci, Co) && !wgrad_by_bricks(g, Ci, Co)) {
+        const WgradCols wc = wgrad_cols_plan(g, Ci, Co, nchunk);
+        float* part_b = part + (size_t)wc.used * 27 * Co * Ci;
+        const unsigned grid = (unsigned)(wc.used * (Ci / 16) * (Co / 16) + 7) / 8 * 8;
+        hipLaunchKernelGGL(k_wgrad_cols<kWgColsR>, dim3(grid), dim3(512),
+                           (size_t)wgrad_cols_lds_bytes(kWgColsR), s, dz, x, xl, g, Ci, Cs, Co, wc.n,
+                           wc.ncol, wc.cpw, wc.used, part, part_b);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        return colsum_wb(part, part_b, wc.used, Ci, Co, 16, dw, db, s, 1);
+    }
+    if (wgrad_buffers(g, Ci, Co)) {
+        // by bricks, within the same partial-sum buffer
         const long long nbk = (long long)((g.W + kRX - 1) / kRX) * ((g.H + kRY - 1) / kRY) *
                               ((g.D + kRZ - 1) / kRZ) * g.B;
-        if (nbk > (1LL << 30)) return hipErrorInvalidValue;
         // about 512 workgroups per launch (two per CU, one round): fewer
         // split-K rows for the column sums, more bricks per workgroup to
         // pipeline
@@ -2679,26 +3001,19 @@ hipError_t wgrad_impl(const uint16_t* dz, const uint16_t* x, const uint16_t* xl,
         const int bpc = (int)((nbk + want - 1) / want);
         const long long used = (nbk + bpc - 1) / bpc;   // <= nchunk
         float* part_b = part + used * 27LL * Co * Ci;
-        const int cg = Co == 16 ? 16 : 32;   // outputs per group
-        for (int co0 = 0; co0 < Co; co0 += cg) {
-            float* pw = part + used * 27LL * co0 * Ci;
-            float* pb = part_b + used * co0;
-            const size_t lds = (size_t)wgrad_brick_lds_bytes(cg);
-            if (cg == 16)
-                hipLaunchKernelGGL(k_wgrad_brick<1>, dim3((unsigned)used, Ci / 16), dim3(256), lds,
-                                   s, dz + co0, x, xl, g, Ci, Cs, bpc, (int)nbk, pw, pb, Co);
-            else
-                hipLaunchKernelGGL(k_wgrad_brick<2>, dim3((unsigned)used, Ci / 16), dim3(256), lds,
-                                   s, dz + co0, x, xl, g, Ci, Cs, bpc, (int)nbk, pw, pb, Co);
-            hipError_t e = hipGetLastError();
-            if (e != hipSuccess) return e;
-        }
-        const int n = 27 * Co * Ci, nbw = (n + 63) / 64;
-        hipLaunchKernelGGL(k_colsum_wb, dim3(nbw + (db ? (Co + 63) / 64 : 0)), dim3(1024), 0, s,
-                           part, part_b, (int)used, n, nbw, Co, dw, db, (Ci << 16) | cg);
-        return hipGetLastError();
+        const dim3 grid((unsigned)used, Ci / 16);
+        const size_t lds = (size_t)wgrad_brick_lds_bytes(Co);
+        if (Co == 16)
+            hipLaunchKernelGGL(k_wgrad_brick<1>, grid, dim3(256), lds, s, dz, x, xl, g, Ci, Cs, bpc,
+                               (int)nbk, part, part_b);
+        else
+            hipLaunchKernelGGL(k_wgrad_brick<2>, grid, dim3(256), lds, s, dz, x, xl, g, Ci, Cs, bpc,
+                               (int)nbk, part, part_b);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        return colsum_wb(part, part_b, (int)used, Ci, Co, Co, dw, db, s);
     }
-    if (Cs != Ci) return hipErrorInvalidValue;   // a concatenation is read in place by bricks only
+    if (Cs != Ci) return hipErrorInvalidValue;   // in place only with 32-bit offsets
     const int tg = wgrad_taps_per_group(Ci, Co);
     const int groups = (27 + tg - 1) / tg;
     if (tg * (Co / 16) * (Ci / 16) > kWgWaves * kWgMaxTiles && tg > 1) return hipErrorInvalidValue;
@@ -2709,10 +3024,7 @@ hipError_t wgrad_impl(const uint16_t* dz, const uint16_t* x, const uint16_t* xl,
                        dz, x, g, Ci, Co, chunk, tg, part, part_b);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const int n = 27 * Co * Ci, nbw = (n + 63) / 64;
-    hipLaunchKernelGGL(k_colsum_wb, dim3(nbw + (db ? (Co + 63) / 64 : 0)), dim3(1024), 0, s, part,
-                       part_b, (int)nchunk, n, nbw, Co, dw, db, (Ci << 16) | Co);
-    return hipGetLastError();
+    return colsum_wb(part, part_b, (int)nchunk, Ci, Co, Co, dw, db, s);
 }
 }  // namespace
 
@@ -2724,7 +3036,7 @@ hipError_t wgrad(const uint16_t* dz, const uint16_t* x, const int* dims, int Ci,
 bool wgrad_cat_supported(int Cs, int Cu, int Co, const int* dims) {
     const Geo g{dims[0], dims[1], dims[2], dims[3]};
     return Cs > 0 && Cu > 0 && Cs % 16 == 0 && Cu % 16 == 0 && ((g.D | g.H | g.W) & 1) == 0 &&
-           wgrad_by_bricks(g, Cs + Cu, Co);
+           (Co == 16 || Co == 32 || Co == 64 || Co == 128) && wgrad_buffers(g, Cs + Cu, Co);
 }
 
 hipError_t wgrad_cat(const uint16_t* dz, const uint16_t* skip, const uint16_t* low,
@@ -2848,7 +3160,7 @@ hipError_t head_bwd(const float* dout, const uint16_t* x, const float* w, long l
 }
 
 hipError_t sum_rows(const float* part, int nrow, int ncol, float* out, hipStream_t s) {
-    hipLaunchKernelGGL(k_colsum, dim3((ncol + 63) / 64), dim3(1024), 0, s, part, nrow, ncol, out, 0);
+    hipLaunchKernelGGL(k_colsum, dim3((ncol + 63) / 64), dim3(1024), 0, s, part, nrow, ncol, out);
     return hipGetLastError();
 }
 
