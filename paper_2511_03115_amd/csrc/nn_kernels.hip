@@ -321,8 +321,9 @@ __global__ void __launch_bounds__(256) k_conv_fwd_halo(const uint16_t* __restric
 
 // ---------------------------------------------------------------------------
 // The halo-brick convolution with the input channel count fixed at compile
-// time, for the few-channel layers with 32 outputs (Ci in {16, 32}; those
-// with 16 outputs take the row-reuse kernel below): the B fragments
+// time, for 16 input channels and groups of 32 outputs (16 outputs take the
+// row-reuse kernel below, 32 inputs the one that marches along z; a K step
+// here is two taps, which may lie in different planes): the B fragments
 // (weights) of the K steps live in
 // registers, read from memory in chunks of CH steps, the next chunk in
 // flight while the current one feeds the matrix cores, and the whole
@@ -609,6 +610,7 @@ __global__ void __launch_bounds__(256) k_conv_fwd_reg(const uint16_t* __restrict
 constexpr int kOob = 0x7ff00000;   // a buffer offset past every operand
 
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
 // Output of the row-reuse kernel: bf16 only (y16), FP32 (y32, added to when
 // accumulate; y16 as well when non-null), or the network's head fused in
@@ -1487,6 +1489,230 @@ __global__ void k_flip_transpose(const uint16_t* w, uint16_t* wt, int Ci, int Co
 }
 
 // ---------------------------------------------------------------------------
+// The convolution of 32 input channels to 32 outputs (or groups of 32,
+// one after the other in the grid), marching along z: a workgroup owns a
+// column of 16 x 8 voxels and n output planes, wave w four of its rows (w / 2)
+// and 16 of the outputs (w % 2).  The wave's 27 weight fragments (A operand,
+// one tap of 32 channels each) stay in registers, and an input fragment (16
+// voxels of a row, B operand) read once from LDS feeds up to nine products:
+// three rows' y taps times three output planes, which slide along (acc[tz] is
+// plane z + 1 - tz; every output takes its taps in ascending order).
+// Input planes go through a ring of three LDS buffers (one barrier per
+// plane), the plane after the next in flight during a plane's products; a lane
+// ends with four consecutive outputs of a voxel, stored from registers.
+// Loads and stores sit behind no branch: with one, the wait counts after it
+// are those of the longer path, and every plane waited for the newest loads
+// (85 us instead of 72).
+//
+// What bounds it: the matrix cores' 1728 clocks per plane and wave, two waves
+// to a SIMD, next to 450 clocks of epilogue each and 8 us for start and end; a
+// workgroup per brick read 6 LDS fragments per 8 products, weights included,
+// with 2-way bank conflicts, and kept the matrix cores 28 % busy.  Here it is 1
+// per 6, and voxels lie 96 bytes apart (16 lanes on distinct banks).
+// 100 x 128 x 128 voxels, 32 -> 32: 128 -> 78 us (1.17 PFLOP/s, 2.7 TB/s);
+// 4 x 64 x 32 x 32, 32 -> 96 in FP32 with the weights' flip: 85 -> 50 us.
+// ---------------------------------------------------------------------------
+constexpr int kMaVox = 10 * 18;          // halo plane
+constexpr int kMaRow = 48;               // elements per voxel: 32 and the pad
+constexpr int kMarchLds = 3 * kMaVox * kMaRow * 2;
+
+enum { kMaBf16 = 0, kMaF32 = 1, kMaBoth = 2, kMaDz = 3 };   // outputs; dz: through ym's LeakyReLU
+
+template <int OUT>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+k_conv_march(const uint16_t* __restrict__ x, const uint16_t* __restrict__ w,
+             const float* __restrict__ bias, Geo g, int Co, int n, float alpha, int act,
+             uint16_t* __restrict__ y16, float* __restrict__ y32,
+             const uint16_t* __restrict__ ym) {
+    constexpr int R = 4, K = 27 * 32, NL = (kMaVox * 4 + 255) / 256;
+    extern __shared__ __align__(16) uint16_t hx[];   // [3][kMaVox][kMaRow]
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, q = lane >> 4;
+    // items: output group fastest, then x, y, z chunk, batch; an XCD (workgroups
+    // go round the 8 in turn) takes consecutive ones, which share halos
+    int r = xcd_contiguous(blockIdx.x, gridDim.x);
+    const int ngr = Co / 32;
+    const int co0 = (r % ngr) * 32 + (wave & 1) * 16;
+    r /= ngr;
+    const int nbx = (g.W + 15) / 16, nby = (g.H + 7) / 8, nbz = (g.D + n - 1) / n;
+    const int x0 = (r % nbx) * 16;
+    r /= nbx;
+    const int y0 = (r % nby) * 8;
+    r /= nby;
+    const int z0 = (r % nbz) * n, b = r / nbz;
+    const int z1 = min(z0 + n, g.D);
+    const int zs = max(z0 - 1, 0);   // input planes zs..z1
+    const __amdgpu_buffer_rsrc_t xr = rsrc16(x, g.nvox() * 32);
+    const __amdgpu_buffer_rsrc_t wr = rsrc16(w, (long long)Co * K);
+
+    bf16x8 wv[27];
+#pragma unroll
+    for (int t = 0; t < 27; ++t)
+        wv[t] = as_bf16x8(__builtin_bit_cast(
+            uint4, __builtin_amdgcn_raw_buffer_load_b128(
+                       wr, ((co0 + (lane & 15)) * K + t * 32 + q * 8) * 2, 0, 0)));
+    // staging: a thread's 16-byte units of a plane, four per voxel
+    const int plane = g.H * g.W * 64;
+    int xo[NL], lo[NL];
+#pragma unroll
+    for (int k = 0; k < NL; ++k) {
+        const int i = tid + 256 * k, v = i >> 2, c = i & 3;
+        const int xx = x0 - 1 + v % 18, yy = y0 - 1 + v / 18;
+        const bool in = v < kMaVox && (unsigned)xx < (unsigned)g.W && (unsigned)yy < (unsigned)g.H;
+        xo[k] = in ? ((b * g.D * g.H + yy) * g.W + xx) * 64 + c * 16 : kOob;
+        lo[k] = v * kMaRow + c * 8;
+    }
+    uint4 rx[NL];
+    auto load_plane = [&](int z) {
+        const unsigned off = z <= z1 && z < g.D ? (unsigned)(z * plane) : (unsigned)kOob;
+#pragma unroll
+        for (int k = 0; k < NL; ++k)
+            rx[k] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(
+                                                  xr, (int)((unsigned)xo[k] + off), 0, 0));
+    };
+    auto store_lds = [&](int buf) {
+#pragma unroll
+        for (int k = 0; k < NL; ++k)
+            if (tid + 256 * k < kMaVox * 4)
+                *reinterpret_cast<uint4*>(hx + buf * kMaVox * kMaRow + lo[k]) = rx[k];
+    };
+
+    f32x4 acc[3][R];   // output plane zs + i in acc[i % 3]
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+#pragma unroll
+        for (int m = 0; m < R; ++m) acc[t][m] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int fb = ((wave >> 1) * R * 18 + (lane & 15)) * kMaRow + q * 8;
+    // the products of input plane zs + i, I = i % 3, with the output planes of
+    // the mask Z (bit tz: plane zs + i + 1 - tz)
+    auto products = [&](auto idx, auto taps) {
+        constexpr int I = decltype(idx)::value, Z = decltype(taps)::value;
+        // a row's fragments are read during the previous row's products
+        bf16x8 f[2][3];
+        auto row = [&](int hr) {
+#pragma unroll
+            for (int tx = 0; tx < 3; ++tx)
+                f[hr & 1][tx] = as_bf16x8(*reinterpret_cast<const uint4*>(
+                    hx + I * kMaVox * kMaRow + fb + (hr * 18 + tx) * kMaRow));
+        };
+        row(0);
+#pragma unroll
+        for (int hr = 0; hr < R + 2; ++hr) {
+            if (hr + 1 < R + 2) row(hr + 1);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int tx = 0; tx < 3; ++tx)
+#pragma unroll
+                for (int ty = 0; ty < 3; ++ty) {
+                    const int m = hr - ty;
+                    if (m < 0 || m >= R) continue;
+#pragma unroll
+                    for (int tz = 0; tz < 3; ++tz)
+                        if ((Z >> tz) & 1) {
+                            f32x4& c = acc[(I + 4 - tz) % 3][m];
+                            c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                wv[tz * 9 + ty * 3 + tx], f[hr & 1][tx], c, 0, 0, 0);
+                        }
+                }
+        }
+    };
+    float bq[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) bq[i] = bias ? bias[co0 + q * 4 + i] : 0.0f;
+    // a lane's output offset in a plane, in elements (no branches around loads
+    // and stores: what is not wanted goes past the end, so that the wait counts
+    // stay exact across the march)
+    const int xx = x0 + (lane & 15), yw = y0 + (wave >> 1) * R;
+    const long long oplane = (long long)g.H * g.W * Co;
+    int yo[R];
+#pragma unroll
+    for (int m = 0; m < R; ++m)
+        yo[m] = xx < g.W && yw + m < g.H ? ((yw + m) * g.W + xx) * Co + co0 + q * 4 : kOob / 4;
+    auto rsrc_plane = [&](const void* p, int z, int size) {
+        return __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<char*>(static_cast<const char*>(p)) + (b * (long long)g.D + z) * oplane * size,
+            0, z >= z0 ? (int)(oplane * size) : 0, 0x00020000);
+    };
+    u32x2 ymk[R];   // kMaDz: the activation's 4 channels, loaded before the products
+    auto load_ym = [&](int z) {
+        const __amdgpu_buffer_rsrc_t yr = rsrc_plane(ym, max(z, 0), 2);
+#pragma unroll
+        for (int m = 0; m < R; ++m)
+            ymk[m] = __builtin_amdgcn_raw_buffer_load_b64(yr, yo[m] * 2, 0, 0);
+    };
+    // plane z of the outputs (none below z0), from its accumulators
+    auto emit = [&](int z, f32x4 (&c)[R]) {
+        const __amdgpu_buffer_rsrc_t hr = rsrc_plane(y16, z, 2), fr = rsrc_plane(y32, z, 4);
+        float v[R][4];
+#pragma unroll
+        for (int m = 0; m < R; ++m)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[m][i] = c[m][i] + bq[i];
+        if (act) {
+            if (alpha <= 1.0f) {
+#pragma unroll
+                for (int m = 0; m < R; ++m)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) v[m][i] = fmaxf(v[m][i], alpha * v[m][i]);
+            } else {
+#pragma unroll
+                for (int m = 0; m < R; ++m)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        v[m][i] = v[m][i] > 0.0f ? v[m][i] : alpha * v[m][i];
+            }
+        }
+#pragma unroll
+        for (int m = 0; m < R; ++m) {
+            if constexpr (OUT == kMaDz) {   // as lrelu_bwd turns v
+                const float yv[4] = {__uint_as_float(ymk[m].x << 16),
+                                     __uint_as_float(ymk[m].x & 0xFFFF0000u),
+                                     __uint_as_float(ymk[m].y << 16),
+                                     __uint_as_float(ymk[m].y & 0xFFFF0000u)};
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[m][i] = yv[i] > 0.0f ? v[m][i] : alpha * v[m][i];
+            }
+            if constexpr (OUT != kMaF32)
+                __builtin_amdgcn_raw_buffer_store_b64(
+                    u32x2{pk_bf16(v[m][0], v[m][1]), pk_bf16(v[m][2], v[m][3])}, hr, yo[m] * 2, 0,
+                    0);
+            if constexpr (OUT == kMaF32 || OUT == kMaBoth)
+                __builtin_amdgcn_raw_buffer_store_b128(
+                    __builtin_bit_cast(u32x4, f32x4{v[m][0], v[m][1], v[m][2], v[m][3]}), fr,
+                    yo[m] * 4, 0, 0);
+        }
+    };
+    // input plane z = zs + i, I = i % 3, from buffer I; the next plane goes to
+    // the next buffer (last read two steps ago), the one after is loaded
+    auto step = [&](int z, auto idx) {
+        constexpr int I = decltype(idx)::value;
+        __syncthreads();   // buffer I is written
+        store_lds((I + 1) % 3);
+        load_plane(z + 2);
+        if constexpr (OUT == kMaDz) load_ym(z - 1);
+#pragma unroll
+        for (int m = 0; m < R; ++m) acc[(I + 1) % 3][m] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (z < z0)
+            products(idx, std::integral_constant<int, 1>{});
+        else if (z >= z1)
+            products(idx, std::integral_constant<int, 4>{});
+        else
+            products(idx, std::integral_constant<int, 7>{});
+        emit(z - 1, acc[(I + 2) % 3]);
+    };
+    load_plane(zs);
+    store_lds(0);
+    load_plane(zs + 1);
+    for (int z = zs;;) {
+        step(z, std::integral_constant<int, 0>{});
+        if (++z > z1) break;
+        step(z, std::integral_constant<int, 1>{});
+        if (++z > z1) break;
+        step(z, std::integral_constant<int, 2>{});
+        if (++z > z1) break;
+    }
+}
+
+// ---------------------------------------------------------------------------
 // Weight and bias gradients where an operand has 2 GiB or more, split over
 // voxel chunks:
 //   part[c][t][co][ci] = sum_{v in chunk c} dz[v][co] x[shift(v, t)][ci],
@@ -1906,7 +2132,7 @@ k_wgrad_cols(const uint16_t* __restrict__ dz, const uint16_t* __restrict__ x,
     const int ci0 = cib * 16, co0 = cob * 16;
     if (c >= used) return;
     const int nbx = (g.W + 15) / 16, nby = (g.H + RY - 1) / RY, nbz = (g.D + n - 1) / n;
-    const int p0 = (2 * c + half_id) * cpw, steps = cpw * (n + 2);
+    const int p0 = (2 * c + half_id) * cpw, p1 = p0 + cpw, steps = cpw * (n + 2);
     const bool lowsrc = ci0 >= Cs;
     const int Cu = Ci - Cs, Dd = g.D >> 1;
     const __amdgpu_buffer_rsrc_t dzr = rsrc16(dz, g.nvox() * Co);
@@ -1965,8 +2191,9 @@ k_wgrad_cols(const uint16_t* __restrict__ dz, const uint16_t* __restrict__ x,
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
             const int z = sz0[s] - 1 + lk;   // input plane; output gradients of plane z + 1
-            xz[s] = z >= 0 && z < g.D ? (z >> low) * xplane : kOob;
-            zz[s] = lk < n && z + 1 < g.D ? (z + 1) * dplane : kOob;
+            const bool on = lp < p1;   // past the last step nothing is read
+            xz[s] = on && z >= 0 && z < g.D ? (z >> low) * xplane : kOob;
+            zz[s] = on && lk < n && z + 1 < g.D ? (z + 1) * dplane : kOob;
         }
 #pragma unroll
         for (int k = 0; k < NXL; ++k)
@@ -2057,16 +2284,19 @@ k_wgrad_cols(const uint16_t* __restrict__ dz, const uint16_t* __restrict__ x,
                 accb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[0][r], ones, accb, 0, 0, 0);
         }
         products(xb);
-        if (st + 1 < steps) store_lds(nb);
-        if (st + 3 < steps) load_raw(nb);
+        // no branch around the loads, so that the wait counts stay exact
+        store_lds(nb);
+        load_raw(nb);
     };
     load_raw(even);   // at least three steps
     load_raw(odd);
     store_lds(even);
     load_raw(even);
-    for (int st = 0; st < steps; st += 2) {
+    for (int st = 0;;) {
         step(st, even, odd);
-        if (st + 1 < steps) step(st + 1, odd, even);
+        if (++st >= steps) break;
+        step(st, odd, even);
+        if (++st >= steps) break;
     }
 
     // the eight waves' sums, nine taps at a time, in a fixed order
@@ -2641,6 +2871,34 @@ hipError_t launch_rows(const uint16_t* x, const uint16_t* xl, const uint16_t* w,
 
 }  // namespace
 
+namespace {
+// k_conv_march: 32-bit offsets (kOob past the operands and past a plane of FP32
+// outputs)
+bool march_fits(const Geo& g, int Ci, int Co) {
+    return Ci == 32 && g.nvox() * std::max(Ci, Co) * 2 <= kOob && (long long)g.H * g.W * Co <= kOob / 4;
+}
+
+// Output planes per column of k_conv_march: a workgroup's time is about that
+// of 4 planes for its start and end, and n + 2 planes, 1.6 times as long with
+// two workgroups on a CU (64 x 32 x 32 x 4 voxels, 32 -> 32: n = 8, 256
+// workgroups 20.2 us, n = 6, 352: 24.3, n = 4, 512: 20.9; 50 x 24 x 40 x 2:
+// n = 4, 234 workgroups 12.7, n = 2, 450: 13.9).
+int march_planes(const Geo& g, int Co) {
+    const long long cols = (long long)((g.W + 15) / 16) * ((g.H + 7) / 8) * g.B * (Co / 32);
+    long long best = 1LL << 60;
+    int pick = g.D;
+    for (int n = 1; n <= g.D; ++n) {
+        const long long items = cols * ((g.D + n - 1) / n);
+        const long long cost = items <= 256 ? 10 * (n + 2) : 16 * (n + 2) * ((items + 511) / 512);
+        if (cost < best) {
+            best = cost;
+            pick = n;
+        }
+    }
+    return pick;
+}
+}  // namespace
+
 bool conv_dz_wide_supported(int Ci, int Co, const int* dims) {
     const Geo g{dims[0], dims[1], dims[2], dims[3]};
     const int nt = (Co + 15) / 16;
@@ -2648,7 +2906,7 @@ bool conv_dz_wide_supported(int Ci, int Co, const int* dims) {
                          ((g.D + kRZ - 1) / kRZ) * g.B < kFewBricks;
     if (Co == 16) return false;
     // the register kernel or the channel-pass kernel takes it (as conv_fwd routes)
-    if (g.nvox() * std::max(Ci, Co) * 2 < (1LL << 31) && (Ci == 16 || Ci == 32) &&
+    if (((Ci == 16 && g.nvox() * std::max(Ci, Co) * 2 < (1LL << 31)) || march_fits(g, Ci, Co)) &&
         (nt == 2 || nt == 6 || (nt == 4 && few)))
         return true;
     return Ci % 32 == 0 && Ci >= 64 && (nt == 2 || nt == 4 || (nt % 2 == 0 && few));
@@ -2696,7 +2954,19 @@ hipError_t conv_fwd(const uint16_t* x, const uint16_t* w, const float* bias, con
         // are too few to fill the device
         const bool few = nbk < kFewBricks;
         if (Ci == 16 && (nt == 2 || nt == 6 || (nt == 4 && few))) LAUNCH_REG(16, 2, 4);
-        else if (Ci == 32 && (nt == 2 || nt == 6 || (nt == 4 && few))) LAUNCH_REG(32, 2, 6);
+        else if (march_fits(g, Ci, Co) && !accumulate && (nt == 2 || nt == 6 || (nt == 4 && few))) {
+            const int n = march_planes(g, Co);
+            const long long items =
+                (long long)((g.W + 15) / 16) * ((g.H + 7) / 8) * g.B * (Co / 32) * ((g.D + n - 1) / n);
+#define LAUNCH_MARCH(OUT)                                                                     \
+    hipLaunchKernelGGL(k_conv_march<OUT>, dim3((unsigned)items), dim3(256), kMarchLds, s, x, w, \
+                       bias, g, Co, n, alpha, act, y16, y32, ym)
+            if (ym) LAUNCH_MARCH(kMaDz);
+            else if (y16 && y32) LAUNCH_MARCH(kMaBoth);
+            else if (y32) LAUNCH_MARCH(kMaF32);
+            else LAUNCH_MARCH(kMaBf16);
+#undef LAUNCH_MARCH
+        }
         else done = false;
 #undef LAUNCH_REG
         if (done) return hipGetLastError();
