@@ -1255,7 +1255,8 @@ __global__ void __launch_bounds__(256) k_conv_in(const uint32_t* __restrict__ x2
 // from L2 kept the vector-memory queue full).  Channels [0, cs) come from x
 // (cs per voxel) and [cs, Ci) from the half-size level xl,
 // nearest-neighbour upsampled (the decoder's concatenation; cs = Ci for a
-// plain input).  K order: pass, tap, channel.
+// plain input).  K order: pass, tap, channel.  For what k_conv_wide's 32-bit
+// offsets do not reach.
 // ---------------------------------------------------------------------------
 template <int NT, int CH, int OCC = 2>
 __global__ void __launch_bounds__(256, OCC) k_conv_fwd_pass(const uint16_t* __restrict__ x,
@@ -1518,6 +1519,50 @@ constexpr int kMarchLds = 3 * kMaVox * kMaRow * 2;
 
 enum { kMaBf16 = 0, kMaF32 = 1, kMaBoth = 2, kMaDz = 3 };   // outputs; dz: through ym's LeakyReLU
 
+// R rows of outputs, four channels of a voxel per lane: bias, LeakyReLU (or
+// its gradient by the activation ymk) and the stores at element offsets yo.
+template <int OUT, int R>
+__device__ __forceinline__ void store_rows(const f32x4 (&c)[R], const float (&bq)[4], int act,
+                                           float alpha, const u32x2 (&ymk)[R],
+                                           __amdgpu_buffer_rsrc_t hr, __amdgpu_buffer_rsrc_t fr,
+                                           const int (&yo)[R]) {
+    float v[R][4];
+#pragma unroll
+    for (int m = 0; m < R; ++m)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[m][i] = c[m][i] + bq[i];
+    if (act) {   // lrelu(), decided once
+        if (alpha <= 1.0f) {
+#pragma unroll
+            for (int m = 0; m < R; ++m)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[m][i] = fmaxf(v[m][i], alpha * v[m][i]);
+        } else {
+#pragma unroll
+            for (int m = 0; m < R; ++m)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[m][i] = v[m][i] > 0.0f ? v[m][i] : alpha * v[m][i];
+        }
+    }
+#pragma unroll
+    for (int m = 0; m < R; ++m) {
+        if constexpr (OUT == kMaDz) {   // as lrelu_bwd turns v
+            const float yv[4] = {
+                __uint_as_float(ymk[m].x << 16), __uint_as_float(ymk[m].x & 0xFFFF0000u),
+                __uint_as_float(ymk[m].y << 16), __uint_as_float(ymk[m].y & 0xFFFF0000u)};
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[m][i] = yv[i] > 0.0f ? v[m][i] : alpha * v[m][i];
+        }
+        if constexpr (OUT != kMaF32)
+            __builtin_amdgcn_raw_buffer_store_b64(
+                u32x2{pk_bf16(v[m][0], v[m][1]), pk_bf16(v[m][2], v[m][3])}, hr, yo[m] * 2, 0, 0);
+        if constexpr (OUT == kMaF32 || OUT == kMaBoth)
+            __builtin_amdgcn_raw_buffer_store_b128(
+                __builtin_bit_cast(u32x4, f32x4{v[m][0], v[m][1], v[m][2], v[m][3]}), fr, yo[m] * 4,
+                0, 0);
+    }
+}
+
 template <int OUT>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
 k_conv_march(const uint16_t* __restrict__ x, const uint16_t* __restrict__ w,
@@ -1640,46 +1685,8 @@ k_conv_march(const uint16_t* __restrict__ x, const uint16_t* __restrict__ w,
             ymk[m] = __builtin_amdgcn_raw_buffer_load_b64(yr, yo[m] * 2, 0, 0);
     };
     // plane z of the outputs (none below z0), from its accumulators
-    auto emit = [&](int z, f32x4 (&c)[R]) {
-        const __amdgpu_buffer_rsrc_t hr = rsrc_plane(y16, z, 2), fr = rsrc_plane(y32, z, 4);
-        float v[R][4];
-#pragma unroll
-        for (int m = 0; m < R; ++m)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) v[m][i] = c[m][i] + bq[i];
-        if (act) {
-            if (alpha <= 1.0f) {
-#pragma unroll
-                for (int m = 0; m < R; ++m)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) v[m][i] = fmaxf(v[m][i], alpha * v[m][i]);
-            } else {
-#pragma unroll
-                for (int m = 0; m < R; ++m)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        v[m][i] = v[m][i] > 0.0f ? v[m][i] : alpha * v[m][i];
-            }
-        }
-#pragma unroll
-        for (int m = 0; m < R; ++m) {
-            if constexpr (OUT == kMaDz) {   // as lrelu_bwd turns v
-                const float yv[4] = {__uint_as_float(ymk[m].x << 16),
-                                     __uint_as_float(ymk[m].x & 0xFFFF0000u),
-                                     __uint_as_float(ymk[m].y << 16),
-                                     __uint_as_float(ymk[m].y & 0xFFFF0000u)};
-#pragma unroll
-                for (int i = 0; i < 4; ++i) v[m][i] = yv[i] > 0.0f ? v[m][i] : alpha * v[m][i];
-            }
-            if constexpr (OUT != kMaF32)
-                __builtin_amdgcn_raw_buffer_store_b64(
-                    u32x2{pk_bf16(v[m][0], v[m][1]), pk_bf16(v[m][2], v[m][3])}, hr, yo[m] * 2, 0,
-                    0);
-            if constexpr (OUT == kMaF32 || OUT == kMaBoth)
-                __builtin_amdgcn_raw_buffer_store_b128(
-                    __builtin_bit_cast(u32x4, f32x4{v[m][0], v[m][1], v[m][2], v[m][3]}), fr,
-                    yo[m] * 4, 0, 0);
-        }
+    auto emit = [&](int z, const f32x4 (&c)[R]) {
+        store_rows<OUT, R>(c, bq, act, alpha, ymk, rsrc_plane(y16, z, 2), rsrc_plane(y32, z, 4), yo);
     };
     // input plane z = zs + i, I = i % 3, from buffer I; the next plane goes to
     // the next buffer (last read two steps ago), the one after is loaded
@@ -1710,6 +1717,195 @@ k_conv_march(const uint16_t* __restrict__ x, const uint16_t* __restrict__ w,
         step(z, std::integral_constant<int, 2>{});
         if (++z > z1) break;
     }
+}
+
+// ---------------------------------------------------------------------------
+// The same for 64 and more input channels (a multiple of 32), 32 outputs or
+// groups of 32: blocks of 16 x 8 voxels and ZB output planes, the channels
+// taken 32 at a time (a pass over the block's ZB + 2 input planes), so that the
+// accumulators hold the block over the passes.  A pass's weights replace the
+// last one's a z tap at a time, when the last plane that needs it is done;
+// the planes of all passes run through one ring of LDS buffers without a gap.
+// Channels [0, cs) come from x (cs per voxel), [cs, Ci) from the half-size
+// level xl, nearest-neighbour upsampled (the decoder's concatenation; cs = Ci
+// for a plain input; cs is a multiple of 32).  K order: pass, tap, channel.
+//
+// What bounds it: the matrix cores and the power they draw (53 % busy, the
+// clock at about 2 GHz).  k_conv_fwd_pass, 6 LDS fragments per 8 products and
+// a barrier per two taps: LDS 58 % busy, nearly half of it bank conflicts,
+// matrix cores 33 %.  100 x 128 x 128 voxels, 96 -> 32: 353 -> 234 us (1.16
+// PFLOP/s); 50 x 64 x 64, 192 -> 64: 191 -> 148; 64 -> 64: 80 -> 60.
+// ---------------------------------------------------------------------------
+template <int ZB>
+constexpr int kWideRing = (ZB + 2) % 3 == 0 ? 3 : 4;   // divides the planes of a pass
+
+template <int ZB, int OUT>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+k_conv_wide(const uint16_t* __restrict__ x, const uint16_t* __restrict__ xl,
+            const uint16_t* __restrict__ w, const float* __restrict__ bias, Geo g, int Ci, int cs,
+            int Co, float alpha, int act, uint16_t* __restrict__ y16, float* __restrict__ y32,
+            const uint16_t* __restrict__ ym) {
+    constexpr int R = 4, S = ZB + 2, NR = kWideRing<ZB>, NL = (kMaVox * 4 + 255) / 256;
+    static_assert(S % NR == 0, "a pass starts on buffer 0");
+    extern __shared__ __align__(16) uint16_t hx[];   // [NR][kMaVox][kMaRow]
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, q = lane >> 4;
+    int r = xcd_contiguous(blockIdx.x, gridDim.x);
+    const int ngr = Co / 32;
+    const int co0 = (r % ngr) * 32 + (wave & 1) * 16;
+    r /= ngr;
+    const int nbx = (g.W + 15) / 16, nby = (g.H + 7) / 8, nbz = (g.D + ZB - 1) / ZB;
+    const int x0 = (r % nbx) * 16;
+    r /= nbx;
+    const int y0 = (r % nby) * 8;
+    r /= nby;
+    const int z0 = (r % nbz) * ZB, b = r / nbz;
+    const int P = Ci / 32, K = 27 * Ci, cu = Ci - cs;
+    const int Dd = g.D >> 1, Hd = g.H >> 1, Wd = g.W >> 1;
+    const __amdgpu_buffer_rsrc_t xr = rsrc16(x, g.nvox() * cs);
+    const __amdgpu_buffer_rsrc_t lr = rsrc16(xl ? xl : x, xl ? (long long)g.B * Dd * Hd * Wd * cu : 0);
+    const __amdgpu_buffer_rsrc_t wr = rsrc16(w, (long long)Co * K);
+
+    // the weights of pass p and z tap tz (zeros past the last pass)
+    bf16x8 wv[27];
+    const int wo = ((co0 + (lane & 15)) * K + q * 8) * 2;
+    auto load_weights = [&](int p, auto tap) {
+        constexpr int T = decltype(tap)::value;
+        const int o = p < P ? wo + p * 64 : kOob;
+#pragma unroll
+        for (int t = 0; t < 9; ++t)
+            wv[T * 9 + t] = as_bf16x8(__builtin_bit_cast(
+                uint4, __builtin_amdgcn_raw_buffer_load_b128(wr, o, (T * 9 + t) * Ci * 2, 0)));
+    };
+    // staging: a thread's 16-byte units of a plane, four per voxel, in x and in xl
+    const int plane = g.H * g.W * cs * 2, planel = Hd * Wd * cu * 2;
+    int xo[NL], xlo[NL], lo[NL];
+#pragma unroll
+    for (int k = 0; k < NL; ++k) {
+        const int i = tid + 256 * k, v = i >> 2, c = i & 3;
+        const int xx = x0 - 1 + v % 18, yy = y0 - 1 + v / 18;
+        const bool in = v < kMaVox && (unsigned)xx < (unsigned)g.W && (unsigned)yy < (unsigned)g.H;
+        xo[k] = in ? ((b * g.D * g.H + yy) * g.W + xx) * cs * 2 + c * 16 : kOob;
+        xlo[k] = in ? ((b * Dd * Hd + (yy >> 1)) * Wd + (xx >> 1)) * cu * 2 + c * 16 : kOob;
+        lo[k] = v * kMaRow + c * 8;
+    }
+    constexpr int NS = S % 2 == 0 ? 2 : 3;   // plane i's registers: set i % NS, two in flight
+    uint4 rx[NS][NL];
+    auto load_plane = [&](auto set, int p, int z) {
+        constexpr int N = decltype(set)::value;
+        const bool in = p < P && z >= 0 && z < g.D, low = p * 32 >= cs;
+        const unsigned off = !in   ? (unsigned)kOob
+                             : low ? (unsigned)((z >> 1) * planel + (p * 32 - cs) * 2)
+                                   : (unsigned)(z * plane + p * 64);
+        const __amdgpu_buffer_rsrc_t rr = low ? lr : xr;
+#pragma unroll
+        for (int k = 0; k < NL; ++k)
+            rx[N][k] = __builtin_bit_cast(
+                uint4, __builtin_amdgcn_raw_buffer_load_b128(
+                           rr, (int)((unsigned)(low ? xlo[k] : xo[k]) + off), 0, 0));
+    };
+    auto store_lds = [&](auto set, int buf) {
+        constexpr int N = decltype(set)::value;
+#pragma unroll
+        for (int k = 0; k < NL; ++k)
+            if (tid + 256 * k < kMaVox * 4)
+                *reinterpret_cast<uint4*>(hx + buf * kMaVox * kMaRow + lo[k]) = rx[N][k];
+    };
+
+    f32x4 acc[ZB][R];
+#pragma unroll
+    for (int o = 0; o < ZB; ++o)
+#pragma unroll
+        for (int m = 0; m < R; ++m) acc[o][m] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int fb = ((wave >> 1) * R * 18 + (lane & 15)) * kMaRow + q * 8;
+    // the products of input plane z0 - 1 + I of a pass
+    auto products = [&](auto idx) {
+        constexpr int I = decltype(idx)::value;
+        bf16x8 f[2][3];   // a row's fragments are read during the previous row's products
+        auto row = [&](int hr) {
+#pragma unroll
+            for (int tx = 0; tx < 3; ++tx)
+                f[hr & 1][tx] = as_bf16x8(*reinterpret_cast<const uint4*>(
+                    hx + (I % NR) * kMaVox * kMaRow + fb + (hr * 18 + tx) * kMaRow));
+        };
+        row(0);
+#pragma unroll
+        for (int hr = 0; hr < R + 2; ++hr) {
+            if (hr + 1 < R + 2) row(hr + 1);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int tx = 0; tx < 3; ++tx)
+#pragma unroll
+                for (int ty = 0; ty < 3; ++ty) {
+                    const int m = hr - ty;
+                    if (m < 0 || m >= R) continue;
+#pragma unroll
+                    for (int tz = 0; tz < 3; ++tz) {
+                        const int o = I - tz;
+                        if (o < 0 || o >= ZB) continue;
+                        acc[o][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                            wv[tz * 9 + ty * 3 + tx], f[hr & 1][tx], acc[o][m], 0, 0, 0);
+                    }
+                }
+        }
+    };
+    // input plane I of pass p; the next plane goes to the next buffer, the one
+    // two after it is loaded; the z taps that no later plane of the pass needs are
+    // replaced by the next pass's
+    auto step = [&](int p, auto idx) {
+        constexpr int I = decltype(idx)::value;
+        __syncthreads();
+        store_lds(std::integral_constant<int, (I + 1) % NS>{}, (I + 1) % NR);
+        load_plane(std::integral_constant<int, (I + 3) % NS>{}, I + 3 < S ? p : p + 1,
+                   z0 + 2 + (I + 3 < S ? I : I - S));
+        products(idx);
+        if constexpr (I == ZB - 1) load_weights(p + 1, std::integral_constant<int, 0>{});
+        if constexpr (I == ZB) load_weights(p + 1, std::integral_constant<int, 1>{});
+        if constexpr (I == ZB + 1) load_weights(p + 1, std::integral_constant<int, 2>{});
+    };
+    load_plane(std::integral_constant<int, 0>{}, 0, z0 - 1);
+    load_plane(std::integral_constant<int, 1>{}, 0, z0);
+    load_weights(0, std::integral_constant<int, 0>{});
+    load_weights(0, std::integral_constant<int, 1>{});
+    load_weights(0, std::integral_constant<int, 2>{});
+    store_lds(std::integral_constant<int, 0>{}, 0);
+    load_plane(std::integral_constant<int, 2 % NS>{}, 0, z0 + 1);
+    for (int p = 0; p < P; ++p) {
+        step(p, std::integral_constant<int, 0>{});
+        step(p, std::integral_constant<int, 1>{});
+        step(p, std::integral_constant<int, 2>{});
+        if constexpr (S > 3) step(p, std::integral_constant<int, 3>{});
+        if constexpr (S > 4) step(p, std::integral_constant<int, 4>{});
+        if constexpr (S > 5) step(p, std::integral_constant<int, 5>{});
+    }
+
+    float bq[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) bq[i] = bias ? bias[co0 + q * 4 + i] : 0.0f;
+    const int xx = x0 + (lane & 15), yw = y0 + (wave >> 1) * R;
+    const long long oplane = (long long)g.H * g.W * Co;
+    int yo[R];
+#pragma unroll
+    for (int m = 0; m < R; ++m)
+        yo[m] = xx < g.W && yw + m < g.H ? ((yw + m) * g.W + xx) * Co + co0 + q * 4 : kOob / 4;
+    auto rsrc_plane = [&](const void* p, int z, int size) {
+        return __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<char*>(static_cast<const char*>(p)) + (b * (long long)g.D + z) * oplane * size,
+            0, z < g.D ? (int)(oplane * size) : 0, 0x00020000);
+    };
+    u32x2 ymk[ZB][R];
+    if constexpr (OUT == kMaDz) {
+#pragma unroll
+        for (int o = 0; o < ZB; ++o) {
+            const __amdgpu_buffer_rsrc_t yr = rsrc_plane(ym, z0 + o, 2);
+#pragma unroll
+            for (int m = 0; m < R; ++m)
+                ymk[o][m] = __builtin_amdgcn_raw_buffer_load_b64(yr, yo[m] * 2, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int o = 0; o < ZB; ++o)
+        store_rows<OUT, R>(acc[o], bq, act, alpha, ymk[o], rsrc_plane(y16, z0 + o, 2),
+                           rsrc_plane(y32, z0 + o, 4), yo);
 }
 
 // ---------------------------------------------------------------------------
@@ -2897,6 +3093,59 @@ int march_planes(const Geo& g, int Co) {
     }
     return pick;
 }
+
+// k_conv_wide: as march_fits, the concatenation's parts in whole passes
+bool wide_fits(const Geo& g, int Ci, int cs, int Co) {
+    return Ci >= 64 && Ci % 32 == 0 && cs % 32 == 0 && Co % 32 == 0 &&
+           g.nvox() * std::max(Ci, Co) * 2 <= kOob && 27LL * Ci * Co * 2 <= kOob &&
+           (long long)g.H * g.W * Co <= kOob / 4;
+}
+
+template <int ZB>
+hipError_t launch_wide(const uint16_t* x, const uint16_t* xl, const uint16_t* w, const float* bias,
+                       const Geo& g, int Ci, int cs, int Co, float alpha, int act, uint16_t* y16,
+                       float* y32, const uint16_t* ym, hipStream_t s) {
+    const long long items =
+        (long long)((g.W + 15) / 16) * ((g.H + 7) / 8) * ((g.D + ZB - 1) / ZB) * g.B * (Co / 32);
+    const size_t lds = (size_t)kWideRing<ZB> * kMaVox * kMaRow * 2;
+    static const hipError_t attr = [&] {
+        if (lds <= 64 * 1024) return hipSuccess;
+        for (const void* f :
+             {(const void*)k_conv_wide<ZB, kMaBf16>, (const void*)k_conv_wide<ZB, kMaF32>,
+              (const void*)k_conv_wide<ZB, kMaBoth>, (const void*)k_conv_wide<ZB, kMaDz>}) {
+            const hipError_t e =
+                hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024);
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    }();
+    if (attr != hipSuccess) return attr;
+#define LAUNCH_WIDE(OUT)                                                                        \
+    hipLaunchKernelGGL((k_conv_wide<ZB, OUT>), dim3((unsigned)items), dim3(256), lds, s, x, xl, w, \
+                       bias, g, Ci, cs, Co, alpha, act, y16, y32, ym)
+    if (ym) LAUNCH_WIDE(kMaDz);
+    else if (y16 && y32) LAUNCH_WIDE(kMaBoth);
+    else if (y32) LAUNCH_WIDE(kMaF32);
+    else LAUNCH_WIDE(kMaBf16);
+#undef LAUNCH_WIDE
+    return hipGetLastError();
+}
+
+// Output planes per block of k_conv_wide: the fewest of 1, 2 and 4 that leave
+// at most one workgroup per CU, else 4 (32 x 16 x 16 x 4 voxels, 64 -> 64:
+// 128 workgroups of 4 planes 18.7 us, 256 of 2 14.5, 512 of 1 19.4; 16 x 8 x 8 x
+// 4, 128 -> 128: 27.8, 20.5 and, 256 of 1, 17.2; 60 x 40 x 24, 64 -> 64: 300 of 4
+// 29.8, 31.3 and 42.5).
+hipError_t conv_wide(const uint16_t* x, const uint16_t* xl, const uint16_t* w, const float* bias,
+                     const Geo& g, int Ci, int cs, int Co, float alpha, int act, uint16_t* y16,
+                     float* y32, const uint16_t* ym, hipStream_t s) {
+    const long long cols = (long long)((g.W + 15) / 16) * ((g.H + 7) / 8) * g.B * (Co / 32);
+    if (cols * g.D <= 256)
+        return launch_wide<1>(x, xl, w, bias, g, Ci, cs, Co, alpha, act, y16, y32, ym, s);
+    if (cols * ((g.D + 1) / 2) <= 256)
+        return launch_wide<2>(x, xl, w, bias, g, Ci, cs, Co, alpha, act, y16, y32, ym, s);
+    return launch_wide<4>(x, xl, w, bias, g, Ci, cs, Co, alpha, act, y16, y32, ym, s);
+}
 }  // namespace
 
 bool conv_dz_wide_supported(int Ci, int Co, const int* dims) {
@@ -2974,6 +3223,8 @@ hipError_t conv_fwd(const uint16_t* x, const uint16_t* w, const float* bias, con
     const bool few = (long long)((g.W + kRX - 1) / kRX) * ((g.H + kRY - 1) / kRY) *
                          ((g.D + kRZ - 1) / kRZ) * g.B < kFewBricks;
     if (Ci % 32 == 0 && Ci >= 64 && (nt == 2 || nt == 4 || (nt % 2 == 0 && few))) {
+        if (wide_fits(g, Ci, Ci, Co) && !accumulate)
+            return conv_wide(x, nullptr, w, bias, g, Ci, Ci, Co, alpha, act, y16, y32, ym, s);
         // wide input, channel passes (on few bricks in groups of 32 outputs)
         const long long nbk = (long long)((g.W + kRX - 1) / kRX) * ((g.H + kRY - 1) / kRY) *
                               ((g.D + kRZ - 1) / kRZ) * g.B;
@@ -3042,6 +3293,9 @@ hipError_t conv_cat_fwd(const uint16_t* skip, const uint16_t* low, const uint16_
     const long long nbk = (long long)((g.W + kRX - 1) / kRX) * ((g.H + kRY - 1) / kRY) *
                           ((g.D + kRZ - 1) / kRZ) * g.B;
     if (Co == 32 || Co == 64) {
+        if (wide_fits(g, Cs + Cu, Cs, Co))
+            return conv_wide(skip, low, w, bias, g, Cs + Cu, Cs, Co, alpha, act, y16, nullptr,
+                             nullptr, s);
         if (Co == 32 || nbk < kFewBricks)   // 64 outputs on few bricks: two groups of 32
             hipLaunchKernelGGL((k_conv_fwd_pass<2, 2>), dim3((unsigned)nbk, Co / 32), dim3(256),
                                pass_lds_bytes(2, 2), s, skip, low, w, bias, g, Cs + Cu, Cs, Co,

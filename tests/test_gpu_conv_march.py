@@ -1,6 +1,7 @@
-"""The 32-channel convolution that marches along z, where its columns can go
-wrong: one voxel, one plane, ragged rows and columns, groups of outputs,
-batches, and the seams between columns of different length."""
+"""The convolution of 32 channels that marches along z, and that of more in
+passes over blocks of planes, where they can go wrong: one voxel, one plane,
+ragged rows, columns and blocks, groups of outputs, batches, and the seams
+between columns and blocks of different length."""
 
 import numpy as np
 import pytest
@@ -12,21 +13,24 @@ from test_gpu_nn import bf16_round, to_bf16_dev
 pytestmark = pytest.mark.gpu
 
 
-def _data(shape, co, seed):
+def _data(shape, ci, co, seed):
     rng = np.random.default_rng(seed)
-    return (bf16_round(rng.normal(size=shape + (32,))),
-            bf16_round(rng.normal(scale=0.2, size=(co, 27, 32))),
+    return (bf16_round(rng.normal(size=shape + (ci,))),
+            bf16_round(rng.normal(scale=0.2, size=(co, 27, ci))),
             rng.normal(size=co).astype(np.float32))
 
 
-@pytest.mark.parametrize("shape,co", [((1, 1, 1, 1), 32), ((1, 1, 8, 16), 32), ((2, 3, 9, 17), 96),
-                                      ((3, 2, 7, 5), 64), ((1, 9, 16, 33), 32),
-                                      ((1, 40, 20, 36), 96)])
-def test_march_against_the_oracle(shape, co):
+@pytest.mark.parametrize("shape,ci,co", [
+    ((1, 1, 1, 1), 32, 32), ((1, 1, 8, 16), 32, 32), ((2, 3, 9, 17), 32, 96),
+    ((3, 2, 7, 5), 32, 64), ((1, 9, 16, 33), 32, 32), ((1, 40, 20, 36), 32, 96),
+    # blocks of one, two and four planes
+    ((1, 1, 1, 1), 64, 32), ((2, 3, 9, 17), 96, 64), ((1, 40, 16, 33), 64, 64),
+    ((2, 21, 25, 36), 64, 64), ((1, 66, 17, 50), 96, 32), ((1, 5, 9, 20), 128, 128)])
+def test_against_the_oracle(shape, ci, co):
     import torch
     from paper_2511_03115_amd import nn
-    x, w, b = _data(shape, co, 7 * co + shape[1])
-    log(f"march shape={shape} co={co}")
+    x, w, b = _data(shape, ci, co, 7 * co + ci + shape[1])
+    log(f"conv shape={shape} ci={ci} co={co}")
     ref = nno.conv3d(x, w, b.astype(np.float64))
     tol = 1e-5 * (nno.conv3d(np.abs(x), np.abs(w), None) + np.abs(b)) + 1e-30   # FP32 sums
     out = lambda dt: torch.full(shape + (co,), np.nan, dtype=dt, device="cuda")
@@ -44,16 +48,18 @@ def test_march_against_the_oracle(shape, co):
         assert torch.equal(torch.where(y32 > 0, y32, alpha * y32).bfloat16(), y16)
 
 
+@pytest.mark.parametrize("ci", [32, 64])
 @pytest.mark.parametrize("depth", [2, 3, 5, 17, 33])
-def test_march_seams(depth):
-    """Output planes away from the cut do not depend on where columns end."""
+def test_seams(depth, ci):
+    """Output planes away from the cut do not depend on where columns and
+    blocks end."""
     import torch
     from paper_2511_03115_amd import nn
-    x, w, b = _data((1, 40, 33, 100), 32, 5)
+    x, w, b = _data((1, 40, 33, 100), ci, 32, 5)
     xd, wd, bd = to_bf16_dev(x), to_bf16_dev(w), torch.from_numpy(b).cuda()
     whole = torch.zeros((1, 40, 33, 100, 32), dtype=torch.float32, device="cuda")
     nn.conv3d_fwd(xd, wd, bd, act=False, out32=whole)
     part = torch.zeros((1, depth, 33, 100, 32), dtype=torch.float32, device="cuda")
     nn.conv3d_fwd(xd[:, :depth].contiguous(), wd, bd, act=False, out32=part)
-    log(f"march seams depth={depth}")
+    log(f"seams depth={depth} ci={ci}")
     assert torch.equal(whole[:, :depth - 1], part[:, :depth - 1])
