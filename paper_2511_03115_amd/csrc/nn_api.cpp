@@ -387,7 +387,8 @@ int alloc_all(sde_nn* n) {
         NN_TRY(dalloc(n, &v.eb, nv * n->c[l]));
         if (l > 0) NN_TRY(dalloc(n, &v.pin, nv * n->c[l - 1]));
         if (l <= L - 2) {
-            if (c.train || !conv_cat_fwd_supported(n->c[l], n->c[l + 1], n->c[l], nv))
+            if (c.train || c.store_concat ||
+                !conv_cat_fwd_supported(n->c[l], n->c[l + 1], n->c[l], nv))
                 NN_TRY(dalloc(n, &v.cat, nv * (n->c[l] + n->c[l + 1])));
             NN_TRY(dalloc(n, &v.da, nv * n->c[l]));
             NN_TRY(dalloc(n, &v.db, nv * n->c[l]));

@@ -63,3 +63,27 @@ def test_seams(depth, ci):
     nn.conv3d_fwd(xd[:, :depth].contiguous(), wd, bd, act=False, out32=part)
     log(f"seams depth={depth} ci={ci}")
     assert torch.equal(whole[:, :depth - 1], part[:, :depth - 1])
+
+
+@pytest.mark.parametrize("B,D,H,W", [(1, 10, 130, 130), (1, 40, 34, 34), (3, 2, 18, 16),
+                                     (1, 2, 2, 2), (2, 64, 16, 32)])
+def test_level0_concatenation(B, D, H, W):
+    """The level-0 decoder convolution that marches along z over the skip and
+    the level below in place, against the stored concatenation's: equal bit
+    for bit, over columns of several lengths."""
+    import torch
+    from paper_2511_03115_amd import nn
+    from test_gpu_nn import _net_inputs, he_params
+    flat = nno.flatten(he_params(2, 16, 16, seed=3), 2, 16, 16).astype(np.float32)
+    dose, rho, _, _ = _net_inputs(B, D, H, W, seed=4)
+    log(f"level-0 concatenation {(B, D, H, W)}")
+    outs = []
+    for stored in (False, True):
+        net = nn.Net(2, 16, 16, 0.01, max_batch=B, max_dims=(D, H, W), train=False,
+                     store_concat=stored)
+        net.set_params(flat)
+        out = torch.zeros((B, D, H, W), dtype=torch.float32, device="cuda")
+        net.forward(torch.from_numpy(dose).cuda(), torch.from_numpy(rho).cuda(), out)
+        outs.append(out.cpu().numpy())
+        net.close()
+    assert np.isfinite(outs[0]).all() and np.array_equal(*outs)
