@@ -1909,6 +1909,203 @@ k_conv_wide(const uint16_t* __restrict__ x, const uint16_t* __restrict__ xl,
 }
 
 // ---------------------------------------------------------------------------
+// The decoder's level-0 convolution, concat[16 of x, 32 upsampled of xl] ->
+// 16 outputs, marching along z: a workgroup owns a column of 16 x 16 voxels and
+// n output planes, a wave four of its rows, with all 42 weight fragments in
+// registers.  The K steps and their order are k_conv_rows' (pairs of (dz, dx,
+// 16-channel block) units, three dy each, from the bias on): pairs 0-3 lie in
+// plane z - 1 of an output plane z, pair 4 half there and half in plane z, 5-8 in
+// plane z, 9-13 in z + 1; pairs 0-3 and 9-12 are of the same units, so a step
+// takes both from one reading, for output planes z + 1 and z - 1.  A row in
+// LDS holds 18 voxels of x (32 bytes each) and the 10 coarse voxels of xl it
+// needs (96 bytes apart, read by two neighbours each).
+//
+// What bounds it: the matrix cores, one wave per SIMD (the weights leave no
+// registers for two), 2688 clocks of a plane's 4600; LDS is busy 45 %.  k_conv_rows
+// stages all 48 channels at full size, half again for the halo planes, and
+// reads 84 fragments per 168 products where this takes 60.  13.1M voxels: 737 ->
+// 460 us (1.18 PFLOP/s); 2.1M: 122 -> 81.  Rows read two groups ahead 8 % slower.
+// ---------------------------------------------------------------------------
+constexpr int kCatRow = 18 * 32 + 10 * 96;        // bytes
+constexpr int kCatPlane = 18 * kCatRow;
+constexpr int kCatLds = 3 * kCatPlane;
+
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
+k_conv_cat16(const uint16_t* __restrict__ x, const uint16_t* __restrict__ xl,
+             const uint16_t* __restrict__ w, const float* __restrict__ bias, Geo g, int n,
+             float alpha, int act, uint16_t* __restrict__ y16) {
+    constexpr int R = 4, K = 27 * 48, NF = 3, NC = 3;   // 16-byte units per thread: x, xl
+    extern __shared__ __align__(16) char hc[];   // [3][18 rows][kCatRow]
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, q = lane >> 4, l = lane & 15;
+    int r = xcd_contiguous(blockIdx.x, gridDim.x);
+    const int nbx = (g.W + 15) / 16, nby = (g.H + 15) / 16, nbz = (g.D + n - 1) / n;
+    const int x0 = (r % nbx) * 16;
+    r /= nbx;
+    const int y0 = (r % nby) * 16;
+    r /= nby;
+    const int z0 = (r % nbz) * n, b = r / nbz, z1 = min(z0 + n, g.D);
+    const int Dd = g.D >> 1, Hd = g.H >> 1, Wd = g.W >> 1;
+    const __amdgpu_buffer_rsrc_t xr = rsrc16(x, g.nvox() * 16);
+    const __amdgpu_buffer_rsrc_t lr = rsrc16(xl, (long long)g.B * Dd * Hd * Wd * 32);
+    const __amdgpu_buffer_rsrc_t wr = rsrc16(w, 16LL * K);
+    const __amdgpu_buffer_rsrc_t yr = rsrc16(y16, g.nvox() * 16);
+
+    // weights of pair p and dy (the padded half of the last pair gets zeros),
+    // and the lane's LDS offset of each pair's unit
+    bf16x8 wv[14][3];
+    int po[14];
+#pragma unroll
+    for (int p = 0; p < 14; ++p) {
+        const int u = 2 * p + (q >> 1), uu = u < 27 ? u : 26;
+        const int dz = u / 9, dx = (u / 3) % 3, cb = u % 3;
+        const int dxr = (uu / 3) % 3, cbr = uu % 3;
+#pragma unroll
+        for (int dy = 0; dy < 3; ++dy) {
+            const int k = (dz * 9 + dy * 3 + dx) * 48 + cb * 16 + (q & 1) * 8;
+            wv[p][dy] = as_bf16x8(__builtin_bit_cast(
+                uint4, __builtin_amdgcn_raw_buffer_load_b128(wr, u < 27 ? (l * K + k) * 2 : kOob, 0,
+                                                             0)));
+        }
+        po[p] = wave * R * kCatRow + (q & 1) * 16 +
+                (cbr == 0 ? (l + dxr) * 32 : 18 * 32 + ((l + dxr + 1) >> 1) * 96 + (cbr - 1) * 32);
+    }
+    // staging: the units of a plane's x part (18 rows of 36) and of its xl part
+    // (18 rows of 40; a coarse row serves two)
+    const int plane = g.H * g.W * 32, planel = Hd * Wd * 64;
+    int xo[NF], co[NC], xd[NF], cd[NC];
+#pragma unroll
+    for (int k = 0; k < NF; ++k) {
+        const int i = tid + 256 * k, row = i / 36, c = i % 36;
+        const int xx = x0 - 1 + (c >> 1), yy = y0 - 1 + row;
+        const bool in = row < 18 && (unsigned)xx < (unsigned)g.W && (unsigned)yy < (unsigned)g.H;
+        xo[k] = in ? ((b * g.D * g.H + yy) * g.W + xx) * 32 + (c & 1) * 16 : kOob;
+        xd[k] = row < 18 ? row * kCatRow + c * 16 : -1;
+    }
+#pragma unroll
+    for (int k = 0; k < NC; ++k) {
+        const int i = tid + 256 * k, row = i / 40, c = i % 40;
+        const int xx = (x0 >> 1) - 1 + (c >> 2), yy = y0 - 1 + row;
+        const bool in = row < 18 && (unsigned)xx < (unsigned)Wd && (unsigned)yy < (unsigned)g.H;
+        co[k] = in ? ((b * Dd * Hd + (yy >> 1)) * Wd + xx) * 64 + (c & 3) * 16 : kOob;
+        cd[k] = row < 18 ? row * kCatRow + 18 * 32 + (c >> 2) * 96 + (c & 3) * 16 : -1;
+    }
+    uint4 rx[2][NF], rc[2][NC];
+    auto load_plane = [&](auto set, int z) {
+        constexpr int S = decltype(set)::value;
+        const bool in = z >= 0 && z < g.D && z <= z1;
+        const unsigned of = in ? (unsigned)(z * plane) : (unsigned)kOob;
+        const unsigned oc = in ? (unsigned)((z >> 1) * planel) : (unsigned)kOob;
+#pragma unroll
+        for (int k = 0; k < NF; ++k)
+            rx[S][k] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(
+                                                     xr, (int)((unsigned)xo[k] + of), 0, 0));
+#pragma unroll
+        for (int k = 0; k < NC; ++k)
+            rc[S][k] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(
+                                                     lr, (int)((unsigned)co[k] + oc), 0, 0));
+    };
+    auto store_lds = [&](auto set, int buf) {
+        constexpr int S = decltype(set)::value;
+#pragma unroll
+        for (int k = 0; k < NF; ++k)
+            if (xd[k] >= 0) *reinterpret_cast<uint4*>(hc + buf * kCatPlane + xd[k]) = rx[S][k];
+#pragma unroll
+        for (int k = 0; k < NC; ++k)
+            if (cd[k] >= 0) *reinterpret_cast<uint4*>(hc + buf * kCatPlane + cd[k]) = rc[S][k];
+    };
+
+    f32x4 bq, acc[3][R];   // output plane z0 - 1 + i in acc[i % 3]
+#pragma unroll
+    for (int i = 0; i < 4; ++i) bq[i] = bias ? bias[q * 4 + i] : 0.0f;
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+#pragma unroll
+        for (int m = 0; m < R; ++m) acc[t][m] = bq;
+    const float slope = act ? alpha : 1.0f;   // r > 0 ? r : slope r
+    const int xx = x0 + l, yw = y0 + wave * R;
+    int yo[R];
+#pragma unroll
+    for (int m = 0; m < R; ++m)
+        yo[m] = xx < g.W && yw + m < g.H ? (((b * g.D) * g.H + yw + m) * g.W + xx) * 32 + q * 8 : kOob;
+    auto emit = [&](int z, const f32x4 (&c)[R]) {
+        const unsigned off = z >= z0 ? (unsigned)(z * plane) : (unsigned)kOob;
+#pragma unroll
+        for (int m = 0; m < R; ++m) {
+            float v[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = c[m][i] > 0.0f ? c[m][i] : slope * c[m][i];
+            __builtin_amdgcn_raw_buffer_store_b64(
+                u32x2{pk_bf16(v[0], v[1]), pk_bf16(v[2], v[3])}, yr, (int)((unsigned)yo[m] + off), 0, 0);
+        }
+    };
+    // input plane z = z0 - 1 + i, I = i % 3, buffer I, register set SE = i % 2
+    auto step = [&](int z, auto idx, auto set, auto nset) {
+        constexpr int I = decltype(idx)::value, J = (I + 2) % 3;   // J: the plane before
+        __syncthreads();
+        f32x4(&up)[R] = acc[(I + 1) % 3];
+        f32x4(&mid)[R] = acc[I];
+        f32x4(&dn)[R] = acc[J];
+#pragma unroll
+        for (int m = 0; m < R; ++m) up[m] = bq;
+        // ten groups of rows, read during the products of the group before
+        bf16x8 f[2][R + 2];
+        auto rows = [&](int gi) {
+            const int p = gi < 4 ? gi : gi == 9 ? 13 : gi;
+            const int o = po[p] + (gi == 4 && q < 2 ? J : I) * kCatPlane;
+#pragma unroll
+            for (int i = 0; i < R + 2; ++i)
+                f[gi & 1][i] = as_bf16x8(*reinterpret_cast<const uint4*>(hc + o + i * kCatRow));
+        };
+        auto mul = [&](int p, int gi, f32x4 (&c)[R]) {
+#pragma unroll
+            for (int dy = 0; dy < 3; ++dy)
+#pragma unroll
+                for (int m = 0; m < R; ++m)
+                    c[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv[p][dy], f[gi & 1][m + dy],
+                                                                   c[m], 0, 0, 0);
+        };
+        rows(0);
+        store_lds(nset, (I + 1) % 3);
+        load_plane(nset, z + 3);
+#pragma unroll
+        for (int gi = 0; gi < 10; ++gi) {
+            if (gi + 1 < 10) rows(gi + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            if (gi < 4) {
+                mul(gi, gi, up);
+                mul(gi + 9, gi, dn);
+            } else if (gi < 9) {
+                mul(gi, gi, mid);
+            } else {
+                mul(13, gi, dn);
+            }
+        }
+        emit(z - 1, dn);
+    };
+    const std::integral_constant<int, 0> c0{};
+    const std::integral_constant<int, 1> c1{};
+    const std::integral_constant<int, 2> c2{};
+    load_plane(c0, z0 - 1);
+    load_plane(c1, z0);
+    store_lds(c0, 0);
+    load_plane(c0, z0 + 1);
+    for (int z = z0 - 1;;) {
+        step(z, c0, c0, c1);
+        if (++z > z1) break;
+        step(z, c1, c1, c0);
+        if (++z > z1) break;
+        step(z, c2, c0, c1);
+        if (++z > z1) break;
+        step(z, c0, c1, c0);
+        if (++z > z1) break;
+        step(z, c1, c0, c1);
+        if (++z > z1) break;
+        step(z, c2, c1, c0);
+        if (++z > z1) break;
+    }
+}
+
+// ---------------------------------------------------------------------------
 // Weight and bias gradients where an operand has 2 GiB or more, split over
 // voxel chunks:
 //   part[c][t][co][ci] = sum_{v in chunk c} dz[v][co] x[shift(v, t)][ci],
@@ -3304,6 +3501,17 @@ hipError_t conv_cat_fwd(const uint16_t* skip, const uint16_t* low, const uint16_
             hipLaunchKernelGGL((k_conv_fwd_pass<4, 2>), dim3((unsigned)nbk), dim3(256),
                                pass_lds_bytes(4, 2), s, skip, low, w, bias, g, Cs + Cu, Cs, Co,
                                alpha, act, y16, nullptr, 0, nullptr);
+        return hipGetLastError();
+    }
+    if (g.nvox() * 32 <= kOob) {
+        static const hipError_t attr = hipFuncSetAttribute(
+            (const void*)k_conv_cat16, hipFuncAttributeMaxDynamicSharedMemorySize, kCatLds);
+        if (attr != hipSuccess) return attr;
+        const long long cols = (long long)((g.W + 15) / 16) * ((g.H + 15) / 16) * g.B;
+        const long long nz = std::max(1LL, std::min((long long)g.D, 256 / cols));
+        const int n = (int)((g.D + nz - 1) / nz);
+        hipLaunchKernelGGL(k_conv_cat16, dim3((unsigned)(cols * ((g.D + n - 1) / n))), dim3(256),
+                           kCatLds, s, skip, low, w, bias, g, n, alpha, act, y16);
         return hipGetLastError();
     }
     return launch_rows<48, 16>(skip, low, w, bias, g, alpha, act, y16, nullptr, 0, s);
