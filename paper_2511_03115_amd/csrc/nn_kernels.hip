@@ -2106,6 +2106,348 @@ k_conv_cat16(const uint16_t* __restrict__ x, const uint16_t* __restrict__ xl,
 }
 
 // ---------------------------------------------------------------------------
+// The 16 -> 16 convolution (or groups of 16 outputs), marching along z: a
+// workgroup owns a column of 16 x 16 voxels and n output planes, a wave four
+// of its rows, the 15 weight fragments in registers.  The K steps and their
+// order are k_conv_rows' (pairs of (dz, dx) units, three dy each, from the bias
+// on): pair 0 lies in plane z - 1 of an output plane z, pair 1 half there and
+// half in plane z, 2 in plane z, 3 and 4 in z + 1; pairs 0 and 3 are of the same
+// units, so a step takes both from one reading, for output planes z + 1 and
+// z - 1.  The outputs are k_conv_rows' (OUT, HeadArgs); the 2 x 2 x 2 sums of
+// kOutPool and kOutUpDz add an even plane's, kept in registers, to the next's.
+//
+// What bounds it: memory, 64 B per voxel, and the epilogue next to 960 clocks
+// of products per plane; k_conv_rows reads every brick's halo planes again (6
+// for 4), this each plane once per column.  13.1M voxels: 235 -> 177 us (4.7
+// TB/s), with the pool 265 -> 203, with the head 232 -> 220; the 32 upsampled
+// outputs of 2.1M voxels (kOutUpDz) 73 -> 57.
+// ---------------------------------------------------------------------------
+constexpr int kM16Row = 18 * 16, kM16Plane = 18 * kM16Row;   // elements
+constexpr int kM16Lds = 3 * kM16Plane * 2;
+
+// p of lane l ^ 1; p plus that of lane l ^ 16, l ^ 32 (within the vector unit:
+// a shuffle goes through LDS)
+__device__ __forceinline__ float lane_xor1(float p) {
+    return __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(p), 0xB1, 0xF, 0xF, true));
+}
+__device__ __forceinline__ float add_xor16(float p) {
+    const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(p), __float_as_uint(p), false, false);
+    return __uint_as_float(s[0]) + __uint_as_float(s[1]);
+}
+__device__ __forceinline__ float add_xor32(float p) {
+    const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(p), __float_as_uint(p), false, false);
+    return __uint_as_float(s[0]) + __uint_as_float(s[1]);
+}
+
+template <int OUT>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+k_conv_march16(const uint16_t* __restrict__ x, const uint16_t* __restrict__ w,
+               const float* __restrict__ bias, Geo g, int n, float alpha, int act,
+               uint16_t* __restrict__ y16, float* __restrict__ y32, HeadArgs head, int ys) {
+    constexpr int R = 4, K = 27 * 16, NL = 3;
+    constexpr bool BLK = OUT == kOutPool || OUT == kOutUpDz;
+    extern __shared__ __align__(16) uint16_t hx[];   // [3][18 rows][18 voxels][16]
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, q = lane >> 4, l = lane & 15;
+    int r = xcd_contiguous(blockIdx.x, gridDim.x);
+    const int ngr = ys / 16, cg = (r % ngr) * 16;
+    r /= ngr;
+    const int nbx = (g.W + 15) / 16, nby = (g.H + 15) / 16, nbz = (g.D + n - 1) / n;
+    const int x0 = (r % nbx) * 16;
+    r /= nbx;
+    const int y0 = (r % nby) * 16;
+    r /= nby;
+    const int z0 = (r % nbz) * n, b = r / nbz, z1 = min(z0 + n, g.D);
+    const Geo gp{g.B, g.D >> 1, g.H >> 1, g.W >> 1};
+    const __amdgpu_buffer_rsrc_t xr = rsrc16(x, g.nvox() * 16);
+    const __amdgpu_buffer_rsrc_t wr = rsrc16(w + (long long)cg * K, 16LL * K);
+    const __amdgpu_buffer_rsrc_t yr = rsrc16(y16, y16 ? g.nvox() * ys : 0);
+
+    // weights of pair p and dy (the padded half of the last pair gets zeros),
+    // and the lane's LDS offset of each pair's unit
+    bf16x8 wv[5][3];
+    int po[5];
+#pragma unroll
+    for (int p = 0; p < 5; ++p) {
+        const int u = 2 * p + (q >> 1), uu = u < 9 ? u : 8;
+#pragma unroll
+        for (int dy = 0; dy < 3; ++dy) {
+            const int k = ((u / 3) * 9 + dy * 3 + u % 3) * 16 + (q & 1) * 8;
+            wv[p][dy] = as_bf16x8(__builtin_bit_cast(
+                uint4, __builtin_amdgcn_raw_buffer_load_b128(wr, u < 9 ? (l * K + k) * 2 : kOob, 0, 0)));
+        }
+        po[p] = wave * R * kM16Row + (l + uu % 3) * 16 + (q & 1) * 8;
+    }
+    const int plane = g.H * g.W * 32;
+    int xo[NL];
+#pragma unroll
+    for (int k = 0; k < NL; ++k) {
+        const int i = tid + 256 * k, row = i / 36, c = i % 36;
+        const int xx = x0 - 1 + (c >> 1), yy = y0 - 1 + row;
+        const bool in = row < 18 && (unsigned)xx < (unsigned)g.W && (unsigned)yy < (unsigned)g.H;
+        xo[k] = in ? ((b * g.D * g.H + yy) * g.W + xx) * 32 + (c & 1) * 16 : kOob;
+    }
+    uint4 rx[2][NL];
+    auto load_plane = [&](auto set, int z) {
+        constexpr int S = decltype(set)::value;
+        const unsigned off = z >= 0 && z < g.D && z <= z1 ? (unsigned)(z * plane) : (unsigned)kOob;
+#pragma unroll
+        for (int k = 0; k < NL; ++k)
+            rx[S][k] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(
+                                                     xr, (int)((unsigned)xo[k] + off), 0, 0));
+    };
+    auto store_lds = [&](auto set, int buf) {
+        constexpr int S = decltype(set)::value;
+#pragma unroll
+        for (int k = 0; k < NL; ++k)
+            if (tid + 256 * k < 18 * 36)
+                *reinterpret_cast<uint4*>(hx + buf * kM16Plane + (tid + 256 * k) * 8) = rx[S][k];
+    };
+
+    f32x4 bq, acc[3][R];   // output plane z0 - 1 + i in acc[i % 3]
+#pragma unroll
+    for (int i = 0; i < 4; ++i) bq[i] = bias ? bias[cg + q * 4 + i] : 0.0f;
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+#pragma unroll
+        for (int m = 0; m < R; ++m) acc[t][m] = bq;
+    const float slope = act ? alpha : 1.0f;   // r > 0 ? r : slope r
+    // the lane's voxels: (xx, yw + m); of a plane the first one's index is
+    // worked out anew, the rows are a scalar stride apart
+    const int xx = x0 + l, yw = __builtin_amdgcn_readfirstlane(y0 + wave * R);
+    const bool xin = xx < g.W;
+    auto first = [&](int z) {
+        asm("" : "+s"(z));
+        return ((b * g.D + z) * g.H + yw) * g.W + xx;
+    };
+    auto inside = [&](int z, int m) { return z >= z0 && yw + m < g.H && xin; };
+    float hw[4] = {0.f, 0.f, 0.f, 0.f}, hb = 0.0f;
+    if constexpr (OUT == kOutHead) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) hw[i] = head.w[q * 4 + i];
+        hb = head.b[0];
+    }
+    // what an output plane needs besides its sums, loaded before the products
+    float res[R];
+    u32x2 ymk[R], ymp[2];
+    f32x4 pp[R / 2];
+    int upo[2];
+    const __amdgpu_buffer_rsrc_t rr_ =
+        OUT == kOutHead ? __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(head.resid), 0,
+                                                            (int)(g.nvox() * 4), 0x00020000)
+                        : rsrc16(head.ym, OUT == kOutDz ? g.nvox() * 16
+                                          : OUT == kOutUpDz ? gp.nvox() * ys : 0);
+    const __amdgpu_buffer_rsrc_t pa_ = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float*>(head.par), 0, OUT == kOutDz && head.par ? (int)(gp.nvox() * 64) : 0,
+        0x00020000);
+    const __amdgpu_buffer_rsrc_t or_ = __builtin_amdgcn_make_buffer_rsrc(
+        head.out, 0, OUT == kOutHead ? (int)(g.nvox() * 4) : 0, 0x00020000);
+    const __amdgpu_buffer_rsrc_t pr =
+        rsrc16(head.pool, BLK && head.pool ? gp.nvox() * (OUT == kOutPool ? 16 : ys) : 0);
+    auto parents = [&](int z) {   // kOutPool, kOutUpDz: byte offsets of the stored parents
+        const int px = xx >> 1;
+#pragma unroll
+        for (int mp = 0; mp < 2; ++mp) {
+            const int py = (yw >> 1) + mp;
+            const bool ok = z >= z0 && !(l & 1) && px < gp.W && py < gp.H;
+            const int pv = ((b * gp.D + (z >> 1)) * gp.H + py) * gp.W + px;
+            upo[mp] = ok ? (OUT == kOutPool ? (pv * 16 + q * 4) * 2 : (pv * ys + cg + q * 4) * 2)
+                         : kOob;
+        }
+    };
+    auto preload = [&](int z, auto par) {
+        constexpr int PAR = decltype(par)::value;   // z & 1 where BLK
+        const int v = first(z);
+        if constexpr (OUT == kOutHead) {
+#pragma unroll
+            for (int m = 0; m < R; ++m)
+                res[m] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
+                    rr_, inside(z, m) ? (v + m * g.W) * 4 : kOob, 0, 0));
+        }
+        if constexpr (OUT == kOutDz) {
+#pragma unroll
+            for (int m = 0; m < R; ++m)
+                ymk[m] = __builtin_amdgcn_raw_buffer_load_b64(
+                    rr_, inside(z, m) ? ((v + m * g.W) * 16 + q * 4) * 2 : kOob, 0, 0);
+#pragma unroll
+            for (int mp = 0; mp < R / 2; ++mp) {
+                const int pv = ((b * gp.D + (z >> 1)) * gp.H + (yw >> 1) + mp) * gp.W + (xx >> 1);
+                pp[mp] = __builtin_bit_cast(
+                    f32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                               pa_, inside(z, 2 * mp) ? (pv * 16 + q * 4) * 4 : kOob, 0, 0));
+            }
+        }
+        if constexpr (OUT == kOutUpDz && PAR == 1) {
+            parents(z);
+#pragma unroll
+            for (int mp = 0; mp < 2; ++mp)
+                ymp[mp] = __builtin_amdgcn_raw_buffer_load_b64(rr_, upo[mp], 0, 0);
+        }
+    };
+    float tprev[2][4] = {};   // BLK: the even plane's 2 x 2 sums
+    auto emit = [&](int z, auto par, const f32x4 (&c)[R]) {
+        constexpr int PAR = decltype(par)::value;
+        const int vf = first(z), hw1 = g.H * g.W;
+        float pc[R][4];
+        const __amdgpu_buffer_rsrc_t fr = __builtin_amdgcn_make_buffer_rsrc(
+            reinterpret_cast<char*>(y32) + (b * (long long)g.D + z) * hw1 * (ys * 4LL), 0,
+            OUT == kOutF32 && z >= z0 ? hw1 * ys * 4 : 0, 0x00020000);
+#pragma unroll
+        for (int m = 0; m < R; ++m) {
+            const bool in = inside(z, m);
+            const int v = vf + m * g.W;
+            float s[4];
+            if constexpr (OUT == kOutDz) {
+                const float yv[4] = {
+                    __uint_as_float(ymk[m].x << 16), __uint_as_float(ymk[m].x & 0xFFFF0000u),
+                    __uint_as_float(ymk[m].y << 16), __uint_as_float(ymk[m].y & 0xFFFF0000u)};
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float t = head.par ? c[m][i] + 0.125f * pp[m >> 1][i] : c[m][i];
+                    s[i] = yv[i] > 0.0f ? t : alpha * t;
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) s[i] = c[m][i] > 0.0f ? c[m][i] : slope * c[m][i];
+            }
+            if constexpr (OUT == kOutUpDz) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) pc[m][i] = s[i];
+                continue;
+            }
+            const uint32_t lo16 = pk_bf16(s[0], s[1]), hi16 = pk_bf16(s[2], s[3]);
+            __builtin_amdgcn_raw_buffer_store_b64(u32x2{lo16, hi16}, yr,
+                                                  in ? (v * ys + cg + q * 4) * 2 : kOob, 0, 0);
+            if constexpr (OUT == kOutF32)
+                __builtin_amdgcn_raw_buffer_store_b128(
+                    __builtin_bit_cast(u32x4, f32x4{s[0], s[1], s[2], s[3]}), fr,
+                    in ? (((yw + m) * g.W + xx) * ys + cg + q * 4) * 4 : kOob, 0, 0);
+            if constexpr (OUT == kOutPool) {
+                pc[m][0] = __uint_as_float(lo16 << 16);
+                pc[m][1] = __uint_as_float(lo16 & 0xFFFF0000u);
+                pc[m][2] = __uint_as_float(hi16 << 16);
+                pc[m][3] = __uint_as_float(hi16 & 0xFFFF0000u);
+            }
+            if constexpr (OUT == kOutHead) {
+                // the head on the stored (bf16) values
+                float p = hw[0] * __uint_as_float(lo16 << 16);
+                p = __builtin_fmaf(hw[1], __uint_as_float(lo16 & 0xFFFF0000u), p);
+                p = __builtin_fmaf(hw[2], __uint_as_float(hi16 << 16), p);
+                p = __builtin_fmaf(hw[3], __uint_as_float(hi16 & 0xFFFF0000u), p);
+                p = add_xor16(p);
+                p = add_xor32(p);
+                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint((hb + res[m]) + p), or_,
+                                                      in && q == 0 ? v * 4 : kOob, 0, 0);
+            }
+        }
+        if constexpr (BLK) {
+            // children (c0 + c1) + (c2 + c3) over x pairs (lanes l, l ^ 1) and
+            // y pairs (rows m, m + 1) of this plane
+            float t[2][4];
+#pragma unroll
+            for (int mp = 0; mp < 2; ++mp)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float a0 = pc[2 * mp][i], a2 = pc[2 * mp + 1][i];
+                    const float a1 = lane_xor1(a0), a3 = lane_xor1(a2);
+                    t[mp][i] = (a0 + a1) + (a2 + a3);
+                }
+            if constexpr (PAR == 0) {
+#pragma unroll
+                for (int mp = 0; mp < 2; ++mp)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) tprev[mp][i] = t[mp][i];
+            } else {
+                if constexpr (OUT == kOutPool) parents(z);
+#pragma unroll
+                for (int mp = 0; mp < 2; ++mp) {
+                    float s[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        s[i] = tprev[mp][i] + t[mp][i];
+                        if constexpr (OUT == kOutPool) {
+                            s[i] *= 0.125f;
+                        } else {
+                            const uint32_t h = i < 2 ? ymp[mp].x : ymp[mp].y;
+                            const float yv = __uint_as_float(i & 1 ? h & 0xFFFF0000u : h << 16);
+                            s[i] = yv > 0.0f ? s[i] : alpha * s[i];
+                        }
+                    }
+                    __builtin_amdgcn_raw_buffer_store_b64(
+                        u32x2{pk_bf16(s[0], s[1]), pk_bf16(s[2], s[3])}, pr, upo[mp], 0, 0);
+                }
+            }
+        }
+    };
+    // input plane z = z0 - 1 + i, I = i % 3, buffer I, register set i % 2 (the
+    // parity of the plane that is done, z - 1, as well: z0 is even where BLK)
+    auto step = [&](int z, auto idx, auto set, auto nset) {
+        constexpr int I = decltype(idx)::value, J = (I + 2) % 3;   // J: the plane before
+        __syncthreads();
+        f32x4(&up)[R] = acc[(I + 1) % 3];
+        f32x4(&mid)[R] = acc[I];
+        f32x4(&dn)[R] = acc[J];
+#pragma unroll
+        for (int m = 0; m < R; ++m) up[m] = bq;
+        // four groups of rows, read during the products of the group before
+        bf16x8 f[2][R + 2];
+        auto rows = [&](int gi) {
+            const int p = gi == 3 ? 4 : gi;
+            const int o = po[p] + (gi == 1 && q < 2 ? J : I) * kM16Plane;
+#pragma unroll
+            for (int i = 0; i < R + 2; ++i)
+                f[gi & 1][i] = as_bf16x8(*reinterpret_cast<const uint4*>(hx + o + i * kM16Row));
+        };
+        auto mul = [&](int p, int gi, f32x4 (&c)[R]) {
+#pragma unroll
+            for (int dy = 0; dy < 3; ++dy)
+#pragma unroll
+                for (int m = 0; m < R; ++m)
+                    c[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv[p][dy], f[gi & 1][m + dy],
+                                                                   c[m], 0, 0, 0);
+        };
+        rows(0);
+        store_lds(nset, (I + 1) % 3);
+        load_plane(nset, z + 3);
+        preload(z - 1, set);
+#pragma unroll
+        for (int gi = 0; gi < 4; ++gi) {
+            if (gi + 1 < 4) rows(gi + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            if (gi == 0) {
+                mul(0, 0, up);
+                mul(3, 0, dn);
+            } else if (gi < 3) {
+                mul(gi, gi, mid);
+            } else {
+                mul(4, 3, dn);
+            }
+        }
+        emit(z - 1, set, dn);
+    };
+    const std::integral_constant<int, 0> c0{};
+    const std::integral_constant<int, 1> c1{};
+    const std::integral_constant<int, 2> c2{};
+    load_plane(c0, z0 - 1);
+    load_plane(c1, z0);
+    store_lds(c0, 0);
+    load_plane(c0, z0 + 1);
+    for (int z = z0 - 1;;) {
+        step(z, c0, c0, c1);
+        if (++z > z1) break;
+        step(z, c1, c1, c0);
+        if (++z > z1) break;
+        step(z, c2, c0, c1);
+        if (++z > z1) break;
+        step(z, c0, c1, c0);
+        if (++z > z1) break;
+        step(z, c1, c0, c1);
+        if (++z > z1) break;
+        step(z, c2, c1, c0);
+        if (++z > z1) break;
+    }
+}
+
+// ---------------------------------------------------------------------------
 // Weight and bias gradients where an operand has 2 GiB or more, split over
 // voxel chunks:
 //   part[c][t][co][ci] = sum_{v in chunk c} dz[v][co] x[shift(v, t)][ci],
@@ -3218,6 +3560,47 @@ inline int blocks_for(long long n, int bs = 256, int cap = 16384) {
     return (int)g;
 }
 
+// Output planes per column (a multiple of `multiple`, which divides D) of
+// k_conv_march, and of k_conv_march16: a workgroup's time is about that
+// of 4 planes for its start and end, and n + 2 planes, 1.6 times as long with
+// two workgroups on a CU (64 x 32 x 32 x 4 voxels, 32 -> 32: n = 8, 256
+// workgroups 20.2 us, n = 6, 352: 24.3, n = 4, 512: 20.9; 50 x 24 x 40 x 2:
+// n = 4, 234 workgroups 12.7, n = 2, 450: 13.9).
+int march_planes(const Geo& g, long long cols, int multiple = 1) {
+    long long best = 1LL << 60;
+    int pick = g.D;
+    for (int n = multiple; n <= g.D; n += multiple) {
+        const long long items = cols * ((g.D + n - 1) / n);
+        const long long cost = items <= 256 ? 10 * (n + 2) : 16 * (n + 2) * ((items + 511) / 512);
+        if (cost < best) {
+            best = cost;
+            pick = n;
+        }
+    }
+    return pick;
+}
+
+// The 16 -> 16 convolution by columns (groups of 16 outputs): 32-bit offsets,
+// kOob past every operand and past a plane of FP32 outputs; and from 2M voxels
+// and groups on (the persistent bricks of k_conv_rows have the shorter start:
+// 100 x 40 x 40 voxels 8.2 us, columns 9.8; 1.6M: 30.2 and 31.7; 2.1M: 36.0 and
+// 33.8; 3.3M: 53.6 and 47.9; 13.1M: 235 and 177).
+bool march16_takes(const Geo& g, int groups) {
+    return g.nvox() * 32 * groups <= kOob && (long long)g.H * g.W * 64 * groups <= kOob &&
+           g.nvox() * groups >= 1LL << 21;
+}
+
+template <int OUT>
+hipError_t launch_march16(const uint16_t* x, const uint16_t* w, const float* bias, const Geo& g,
+                          float alpha, int act, uint16_t* y16, float* y32, hipStream_t s,
+                          HeadArgs head, int groups) {
+    const long long cols = (long long)((g.W + 15) / 16) * ((g.H + 15) / 16) * g.B * groups;
+    const int n = march_planes(g, cols, OUT == kOutPool || OUT == kOutUpDz ? 2 : 1);
+    hipLaunchKernelGGL(k_conv_march16<OUT>, dim3((unsigned)(cols * ((g.D + n - 1) / n))), dim3(256),
+                       kM16Lds, s, x, w, bias, g, n, alpha, act, y16, y32, head, 16 * groups);
+    return hipGetLastError();
+}
+
 // The persistent row-reuse convolution: as many workgroups as the device
 // holds at once (the occupancy the compiler's register and LDS use allows),
 // at most one per brick.
@@ -3226,6 +3609,9 @@ hipError_t launch_rows_as(const uint16_t* x, const uint16_t* xl, const uint16_t*
                           const float* bias, Geo g, float alpha, int act, uint16_t* y16,
                           float* y32, int accumulate, hipStream_t s, HeadArgs head = {},
                           int groups = 1) {
+    if constexpr (CI == 16)
+        if (march16_takes(g, groups) && !accumulate)
+            return launch_march16<OUT>(x, w, bias, g, alpha, act, y16, y32, s, head, groups);
     constexpr bool F32 = OUT == kOutF32;
     constexpr size_t lds = ((size_t)kRVox * brick_row(CI) + 256 * 8) * sizeof(uint16_t);
     static const int cap = [] {
@@ -3269,26 +3655,6 @@ namespace {
 // outputs)
 bool march_fits(const Geo& g, int Ci, int Co) {
     return Ci == 32 && g.nvox() * std::max(Ci, Co) * 2 <= kOob && (long long)g.H * g.W * Co <= kOob / 4;
-}
-
-// Output planes per column of k_conv_march: a workgroup's time is about that
-// of 4 planes for its start and end, and n + 2 planes, 1.6 times as long with
-// two workgroups on a CU (64 x 32 x 32 x 4 voxels, 32 -> 32: n = 8, 256
-// workgroups 20.2 us, n = 6, 352: 24.3, n = 4, 512: 20.9; 50 x 24 x 40 x 2:
-// n = 4, 234 workgroups 12.7, n = 2, 450: 13.9).
-int march_planes(const Geo& g, int Co) {
-    const long long cols = (long long)((g.W + 15) / 16) * ((g.H + 7) / 8) * g.B * (Co / 32);
-    long long best = 1LL << 60;
-    int pick = g.D;
-    for (int n = 1; n <= g.D; ++n) {
-        const long long items = cols * ((g.D + n - 1) / n);
-        const long long cost = items <= 256 ? 10 * (n + 2) : 16 * (n + 2) * ((items + 511) / 512);
-        if (cost < best) {
-            best = cost;
-            pick = n;
-        }
-    }
-    return pick;
 }
 
 // k_conv_wide: as march_fits, the concatenation's parts in whole passes
@@ -3401,9 +3767,9 @@ hipError_t conv_fwd(const uint16_t* x, const uint16_t* w, const float* bias, con
         const bool few = nbk < kFewBricks;
         if (Ci == 16 && (nt == 2 || nt == 6 || (nt == 4 && few))) LAUNCH_REG(16, 2, 4);
         else if (march_fits(g, Ci, Co) && !accumulate && (nt == 2 || nt == 6 || (nt == 4 && few))) {
-            const int n = march_planes(g, Co);
-            const long long items =
-                (long long)((g.W + 15) / 16) * ((g.H + 7) / 8) * g.B * (Co / 32) * ((g.D + n - 1) / n);
+            const long long cols = (long long)((g.W + 15) / 16) * ((g.H + 7) / 8) * g.B * (Co / 32);
+            const int n = march_planes(g, cols);
+            const long long items = cols * ((g.D + n - 1) / n);
 #define LAUNCH_MARCH(OUT)                                                                     \
     hipLaunchKernelGGL(k_conv_march<OUT>, dim3((unsigned)items), dim3(256), kMarchLds, s, x, w, \
                        bias, g, Co, n, alpha, act, y16, y32, ym)
