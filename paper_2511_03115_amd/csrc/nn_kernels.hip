@@ -3095,31 +3095,39 @@ __global__ void __launch_bounds__(1024) k_colsum(const float* part, int nrow, in
 // The weight and bias gradients' column sums in one launch: workgroups
 // [0, nbw) sum the weight partials (columns (t, co, ci), written to
 // dW[co][t][ci]), the rest the bias partials; each column in a fixed order.
-// Bound by the latency of a thread's row loads: 512 rows of 6912 columns with
-// one load in flight 11.6 us, 256 rows with eight 4.
-__global__ void __launch_bounds__(256) k_colsum_wb(const float* part, const float* part_b,
-                                                   int nrow, int ncol, int nbw, int Co, float* dw,
-                                                   float* db, int ci_co, int ngr, int frag) {
-    // a workgroup: 256 / ngr columns x ngr row groups (row group g sums rows
+// Bound by the latency of a thread's row loads, eight in flight: 512 rows of
+// 6912 columns with one at a time 11.6 us, 256 rows 3.5; 60 rows of 27648
+// columns 3.3 and 2.8.
+__global__ void __launch_bounds__(1024) k_colsum_wb(const float* part, const float* part_b,
+                                                    int nrow, int ncol, int nbw, int Co, float* dw,
+                                                    float* db, int ci_co, int lcol, int frag) {
+    // a workgroup: 2^lcol columns x ngr row groups (row group g sums rows
     // g, g + ngr, ..., eight loads in flight), the ngr partial sums then added
     // in a fixed order.  The layer's Co outputs come in groups of
     // cg = ci_co & 0xFFFF (each group's partials [row][t][co][ci] and bias
     // partials [row][co] one after the other); column c < ncol = 27 Co Ci is
     // (group, t, co, ci).
-    __shared__ float red[256];
+    __shared__ float red[1024];
     const bool wpart = (int)blockIdx.x < nbw;
     const int Ci = ci_co >> 16, cg = ci_co & 0xFFFF;
-    const int cpb = 256 / ngr, o = threadIdx.x % cpb, gr = threadIdx.x / cpb;
+    const int cpb = 1 << lcol, ngr = blockDim.x >> lcol;
+    const int o = threadIdx.x & (cpb - 1), gr = threadIdx.x >> lcol;
     const int c = (wpart ? (int)blockIdx.x : (int)blockIdx.x - nbw) * cpb + o;
     const int nc = wpart ? ncol : Co;
     const int ng = 27 * cg * Ci;   // weight columns per group
-    const int grp = wpart ? c / ng : c / cg, cc = wpart ? c - grp * ng : c - grp * cg;
+    const int grp = cg == Co ? 0 : wpart ? c / ng : c / cg, cc = wpart ? c - grp * ng : c - grp * cg;
     const float* src = wpart ? part + (size_t)grp * nrow * ng : part_b + (size_t)grp * nrow * cg;
     const int stride = wpart ? ng : cg;
     float s = 0.0f;
     if (c < nc) {
-#pragma unroll 8
-        for (int r = gr; r < nrow; r += ngr) s += src[(size_t)r * stride + cc];
+        for (int r0 = gr; r0 < nrow; r0 += 8 * ngr) {
+            float v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                v[u] = src[(size_t)min(r0 + u * ngr, nrow - 1) * stride + cc];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) s += r0 + u * ngr < nrow ? v[u] : 0.0f;
+        }
     }
     red[threadIdx.x] = s;
     __syncthreads();
@@ -4011,10 +4019,10 @@ namespace {
 bool wgrad_buffers(const Geo& g, int Ci, int Co) { return g.nvox() * std::max(Ci, Co) * 2 <= kOob; }
 
 // The smallest layers with 16 or 32 outputs go by bricks: columns have the
-// longer start and end (11.5k voxels, 32 -> 32 channels: bricks 14 us, columns
-// 16; 16.8k: 20 and 17; 16 -> 16 at 16.8k: 13 and 15, at 48k: 19 and 17).
+// longer start and end (8.2k voxels, 32 -> 32 channels: bricks 14 us, columns
+// 16; 16.8k: 20 and 18; 48 -> 16 at 25.6k: 18.5 and 19.4, at 48k: 22 and 20).
 bool wgrad_by_bricks(const Geo& g, int Ci, int Co) {
-    return (Co == 16 || Co == 32) && g.nvox() * (Ci / 16) * (Co / 16) < 48000;
+    return (Co == 16 || Co == 32) && g.nvox() * (Ci / 16) * (Co / 16) < 80000;
 }
 
 // The split of k_wgrad_cols: n planes per column, ncol columns, cpw pairs of
@@ -4047,11 +4055,13 @@ WgradCols wgrad_cols_plan(const Geo& g, int Ci, int Co, long long max_used) {
 // dw and db (nullable) from nrow rows of partial sums, outputs in groups of cg
 hipError_t colsum_wb(const float* part, const float* part_b, int nrow, int Ci, int Co, int cg,
                      float* dw, float* db, hipStream_t s, int frag = 0) {
-    // row groups: enough that a thread sums about 32 rows
-    const int ngr = nrow <= 32 ? 1 : nrow <= 64 ? 2 : nrow <= 128 ? 4 : nrow <= 256 ? 8 : 16;
-    const int n = 27 * Co * Ci, cpb = 256 / ngr, nbw = (n + cpb - 1) / cpb;
-    hipLaunchKernelGGL(k_colsum_wb, dim3(nbw + (db ? (Co + cpb - 1) / cpb : 0)), dim3(256), 0, s,
-                       part, part_b, nrow, n, nbw, Co, dw, db, (Ci << 16) | cg, ngr, frag);
+    // row groups: a thread sums the 8 rows it has in flight at once, up to 16
+    // groups (120 rows by 4 groups: 0.5 us slower)
+    const int ngr = nrow <= 8 ? 1 : nrow <= 16 ? 2 : nrow <= 32 ? 4 : nrow <= 64 ? 8 : 16;
+    const int lcol = ngr == 1 ? 8 : ngr == 2 ? 7 : 6, cpb = 1 << lcol;
+    const int n = 27 * Co * Ci, nbw = (n + cpb - 1) / cpb;
+    hipLaunchKernelGGL(k_colsum_wb, dim3(nbw + (db ? (Co + cpb - 1) / cpb : 0)), dim3(cpb * ngr), 0, s,
+                       part, part_b, nrow, n, nbw, Co, dw, db, (Ci << 16) | cg, lcol, frag);
     return hipGetLastError();
 }
 

@@ -16,7 +16,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("shape,ci,co", [
     ((1, 1, 1, 1), 64, 64), ((1, 1, 7, 15), 64, 48), ((1, 2, 8, 16), 64, 64),
     ((2, 3, 1, 33), 16, 80), ((3, 5, 9, 17), 96, 64), ((1, 3, 33, 5), 128, 64),
-    ((2, 40, 17, 40), 16, 16), ((1, 97, 16, 33), 16, 16), ((5, 13, 25, 31), 16, 32),
+    ((2, 61, 17, 40), 16, 16), ((1, 161, 16, 33), 16, 16), ((5, 13, 25, 31), 16, 32),
     ((1, 70, 8, 50), 32, 32), ((2, 19, 24, 40), 64, 128), ((7, 4, 20, 20), 48, 64)])
 def test_wgrad_by_columns(shape, ci, co):
     import torch
