@@ -1720,6 +1720,202 @@ k_conv_march(const uint16_t* __restrict__ x, const uint16_t* __restrict__ w,
 }
 
 // ---------------------------------------------------------------------------
+// The convolution of 16 input channels to groups of 32 outputs, marching along
+// z like k_conv_march: a workgroup owns a column of 16 x 8 voxels, wave w four
+// of its rows (w / 2) and 16 of the outputs (w % 2).  A K step is two taps, as
+// in k_conv_fwd_reg and in its order; of a plane's fragments (the voxels of a
+// row under two taps) those of x taps 0, 1 (A) and 1, 2 (B), and of x tap 2 with
+// tap 0 of the next row (C), serve several rows and output planes; M is tap 8
+// of the plane before with tap 9, D tap 26 alone: 25 fragments per 56 products.
+// What bounds it: memory next to the matrix cores (96 B per voxel); as brick
+// kernel 7 fragments per 8 products, weights included, 20 % of them conflicts.
+// 100 x 128 x 128 voxels, 16 -> 32: 74 -> 48 us (3.3 TB/s, 950 TFLOP/s).
+// ---------------------------------------------------------------------------
+constexpr int kMhPlane = 10 * 18 * 16;   // elements
+constexpr int kMhLds = 3 * kMhPlane * 2;
+
+template <int OUT>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+k_conv_march_pairs(const uint16_t* __restrict__ x, const uint16_t* __restrict__ w,
+             const float* __restrict__ bias, Geo g, int Co, int n, float alpha, int act,
+             uint16_t* __restrict__ y16, float* __restrict__ y32,
+             const uint16_t* __restrict__ ym) {
+    constexpr int R = 4, K = 27 * 16, NL = (kMaVox * 2 + 255) / 256;
+    extern __shared__ __align__(16) uint16_t hx[];   // [3][10 rows][18 voxels][16]
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, q = lane >> 4, l = lane & 15;
+    // items: output group fastest, then x, y, z chunk, batch; an XCD (workgroups
+    // go round the 8 in turn) takes consecutive ones, which share halos
+    int r = xcd_contiguous(blockIdx.x, gridDim.x);
+    const int ngr = Co / 32;
+    const int co0 = (r % ngr) * 32 + (wave & 1) * 16;
+    r /= ngr;
+    const int nbx = (g.W + 15) / 16, nby = (g.H + 7) / 8, nbz = (g.D + n - 1) / n;
+    const int x0 = (r % nbx) * 16;
+    r /= nbx;
+    const int y0 = (r % nby) * 8;
+    r /= nby;
+    const int z0 = (r % nbz) * n, b = r / nbz;
+    const int z1 = min(z0 + n, g.D);
+    const __amdgpu_buffer_rsrc_t xr = rsrc16(x, g.nvox() * 16);
+    const __amdgpu_buffer_rsrc_t wr = rsrc16(w, (long long)Co * K);
+
+    bf16x8 wv[14];   // the padded half of the last step gets zeros
+#pragma unroll
+    for (int s = 0; s < 14; ++s) {
+        const int t = 2 * s + (q >> 1);
+        wv[s] = as_bf16x8(__builtin_bit_cast(
+            uint4, __builtin_amdgcn_raw_buffer_load_b128(
+                       wr, t < 27 ? ((co0 + l) * K + t * 16 + (q & 1) * 8) * 2 : kOob, 0, 0)));
+    }
+    // staging: a thread's 16-byte units of a plane, two per voxel
+    const int plane = g.H * g.W * 32;
+    int xo[NL];
+#pragma unroll
+    for (int k = 0; k < NL; ++k) {
+        const int i = tid + 256 * k, v = i >> 1, c = i & 1;
+        const int xx = x0 - 1 + v % 18, yy = y0 - 1 + v / 18;
+        const bool in = v < kMaVox && (unsigned)xx < (unsigned)g.W && (unsigned)yy < (unsigned)g.H;
+        xo[k] = in ? ((b * g.D * g.H + yy) * g.W + xx) * 32 + c * 16 : kOob;
+    }
+    uint4 rx[2][NL];
+    auto load_plane = [&](auto set, int z) {
+        constexpr int S = decltype(set)::value;
+        const unsigned off = z >= 0 && z <= z1 && z < g.D ? (unsigned)(z * plane) : (unsigned)kOob;
+#pragma unroll
+        for (int k = 0; k < NL; ++k)
+            rx[S][k] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(
+                                                  xr, (int)((unsigned)xo[k] + off), 0, 0));
+    };
+    auto store_lds = [&](auto set, int buf) {
+        constexpr int S = decltype(set)::value;
+#pragma unroll
+        for (int k = 0; k < NL; ++k)
+            if (tid + 256 * k < kMaVox * 2)
+                *reinterpret_cast<uint4*>(hx + buf * kMhPlane + (tid + 256 * k) * 8) = rx[S][k];
+    };
+
+    f32x4 acc[3][R];   // output plane z0 - 1 + i in acc[i % 3]
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+#pragma unroll
+        for (int m = 0; m < R; ++m) acc[t][m] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // the lane's LDS offsets (elements) of a fragment's row 0
+    const int fb = ((wave >> 1) * R * 18 + l) * 16 + (q & 1) * 8;
+    const bool hi = q >= 2;
+    const int oA = fb + (hi ? 16 : 0), oB = oA + 16, oC = fb + (hi ? 18 * 16 : 32),
+              oD = fb + 32;
+    // input plane z = z0 - 1 + i, I = i % 3: steps 0-3 for output plane z + 1, 4-8
+    // for z, 9-13 for z - 1, a row at a time
+    auto products = [&](auto idx) {
+        constexpr int I = decltype(idx)::value, J = (I + 2) % 3;   // J: the plane before
+        f32x4(&up)[R] = acc[(I + 1) % 3];
+        f32x4(&mid)[R] = acc[I];
+        f32x4(&dn)[R] = acc[J];
+        const int oM = (hi ? fb + I * kMhPlane : fb + 2 * 18 * 16 + 32 + J * kMhPlane);
+        bf16x8 A[R + 2], B[R + 2], C[R + 1], M[R], D[R];
+        auto rd = [&](int o) { return as_bf16x8(*reinterpret_cast<const uint4*>(hx + o)); };
+        auto fetch = [&](int m) {   // what row m needs beyond row m - 1
+            A[m + 2] = rd(oA + I * kMhPlane + (m + 2) * 18 * 16);
+            B[m + 2] = rd(oB + I * kMhPlane + (m + 2) * 18 * 16);
+            C[m + 1] = rd(oC + I * kMhPlane + (m + 1) * 18 * 16);
+            M[m] = rd(oM + m * 18 * 16);
+            const uint4 d = *reinterpret_cast<const uint4*>(hx + oD + I * kMhPlane + (m + 2) * 18 * 16);
+            D[m] = as_bf16x8(hi ? make_uint4(0, 0, 0, 0) : d);   // no tap 27
+        };
+        auto mul = [&](int s, const bf16x8& f, f32x4& c) {
+            c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wv[s], f, c, 0, 0, 0);
+        };
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            A[h] = rd(oA + I * kMhPlane + h * 18 * 16);
+            B[h] = rd(oB + I * kMhPlane + h * 18 * 16);
+        }
+        C[0] = rd(oC + I * kMhPlane);
+        fetch(0);
+#pragma unroll
+        for (int m = 0; m < R; ++m) {
+            if (m + 1 < R) fetch(m + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            mul(0, A[m], up[m]);
+            mul(4, M[m], mid[m]);
+            mul(9, A[m], dn[m]);
+            mul(1, C[m], up[m]);
+            mul(5, B[m], mid[m]);
+            mul(10, C[m], dn[m]);
+            mul(2, B[m + 1], up[m]);
+            mul(6, A[m + 1], mid[m]);
+            mul(11, B[m + 1], dn[m]);
+            mul(3, A[m + 2], up[m]);
+            mul(7, C[m + 1], mid[m]);
+            mul(12, A[m + 2], dn[m]);
+            mul(8, B[m + 2], mid[m]);
+            mul(13, D[m], dn[m]);
+        }
+    };
+    float bq[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) bq[i] = bias ? bias[co0 + q * 4 + i] : 0.0f;
+    // a lane's output offset in a plane, in elements (no branches around loads
+    // and stores: what is not wanted goes past the end, so that the wait counts
+    // stay exact across the march)
+    const int xx = x0 + (lane & 15), yw = y0 + (wave >> 1) * R;
+    const long long oplane = (long long)g.H * g.W * Co;
+    int yo[R];
+#pragma unroll
+    for (int m = 0; m < R; ++m)
+        yo[m] = xx < g.W && yw + m < g.H ? ((yw + m) * g.W + xx) * Co + co0 + q * 4 : kOob / 4;
+    auto rsrc_plane = [&](const void* p, int z, int size) {
+        return __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<char*>(static_cast<const char*>(p)) + (b * (long long)g.D + z) * oplane * size,
+            0, z >= z0 ? (int)(oplane * size) : 0, 0x00020000);
+    };
+    u32x2 ymk[R];   // kMaDz: the activation's 4 channels, loaded before the products
+    auto load_ym = [&](int z) {
+        const __amdgpu_buffer_rsrc_t yr = rsrc_plane(ym, max(z, 0), 2);
+#pragma unroll
+        for (int m = 0; m < R; ++m)
+            ymk[m] = __builtin_amdgcn_raw_buffer_load_b64(yr, yo[m] * 2, 0, 0);
+    };
+    // plane z of the outputs (none below z0), from its accumulators
+    auto emit = [&](int z, const f32x4 (&c)[R]) {
+        store_rows<OUT, R>(c, bq, act, alpha, ymk, rsrc_plane(y16, z, 2), rsrc_plane(y32, z, 4), yo);
+    };
+    // the next plane goes to the next buffer, the one two after it is loaded
+    auto step = [&](int z, auto idx, auto nset) {
+        constexpr int I = decltype(idx)::value;
+        __syncthreads();   // buffer I is written
+        store_lds(nset, (I + 1) % 3);
+        load_plane(nset, z + 3);
+        if constexpr (OUT == kMaDz) load_ym(z - 1);
+#pragma unroll
+        for (int m = 0; m < R; ++m) acc[(I + 1) % 3][m] = f32x4{0.f, 0.f, 0.f, 0.f};
+        products(idx);
+        emit(z - 1, acc[(I + 2) % 3]);
+    };
+    const std::integral_constant<int, 0> c0{};
+    const std::integral_constant<int, 1> c1{};
+    const std::integral_constant<int, 2> c2{};
+    load_plane(c0, z0 - 1);
+    load_plane(c1, z0);
+    store_lds(c0, 0);
+    load_plane(c0, z0 + 1);
+    for (int z = z0 - 1;;) {
+        step(z, c0, c1);
+        if (++z > z1) break;
+        step(z, c1, c0);
+        if (++z > z1) break;
+        step(z, c2, c1);
+        if (++z > z1) break;
+        step(z, c0, c0);
+        if (++z > z1) break;
+        step(z, c1, c1);
+        if (++z > z1) break;
+        step(z, c2, c0);
+        if (++z > z1) break;
+    }
+}
+
+// ---------------------------------------------------------------------------
 // The same for 64 and more input channels (a multiple of 32), 32 outputs or
 // groups of 32: blocks of 16 x 8 voxels and ZB output planes, the channels
 // taken 32 at a time (a pass over the block's ZB + 2 input planes), so that the
@@ -3662,7 +3858,7 @@ namespace {
 // k_conv_march: 32-bit offsets (kOob past the operands and past a plane of FP32
 // outputs)
 bool march_fits(const Geo& g, int Ci, int Co) {
-    return Ci == 32 && g.nvox() * std::max(Ci, Co) * 2 <= kOob && (long long)g.H * g.W * Co <= kOob / 4;
+    return g.nvox() * std::max(Ci, Co) * 2 <= kOob && (long long)g.H * g.W * Co <= kOob / 4;
 }
 
 // k_conv_wide: as march_fits, the concatenation's parts in whole passes
@@ -3726,7 +3922,8 @@ bool conv_dz_wide_supported(int Ci, int Co, const int* dims) {
                          ((g.D + kRZ - 1) / kRZ) * g.B < kFewBricks;
     if (Co == 16) return false;
     // the register kernel or the channel-pass kernel takes it (as conv_fwd routes)
-    if (((Ci == 16 && g.nvox() * std::max(Ci, Co) * 2 < (1LL << 31)) || march_fits(g, Ci, Co)) &&
+    if (((Ci == 16 && g.nvox() * std::max(Ci, Co) * 2 < (1LL << 31)) ||
+         (Ci == 32 && march_fits(g, Ci, Co))) &&
         (nt == 2 || nt == 6 || (nt == 4 && few)))
         return true;
     return Ci % 32 == 0 && Ci >= 64 && (nt == 2 || nt == 4 || (nt % 2 == 0 && few));
@@ -3773,8 +3970,27 @@ hipError_t conv_fwd(const uint16_t* x, const uint16_t* w, const float* bias, con
         // 32 outputs, 96 as three groups of 32, or 64 as two when the bricks
         // are too few to fill the device
         const bool few = nbk < kFewBricks;
-        if (Ci == 16 && (nt == 2 || nt == 6 || (nt == 4 && few))) LAUNCH_REG(16, 2, 4);
-        else if (march_fits(g, Ci, Co) && !accumulate && (nt == 2 || nt == 6 || (nt == 4 && few))) {
+        const bool groups32 = nt == 2 || nt == 6 || (nt == 4 && few);
+        // 16 inputs: by columns, but for 64k to 170k voxels and groups, where bricks
+        // are a little faster (96k voxels 10.6 us, columns 11.1; 160k: 12.9 and
+        // 13.5; 17k: 7.6 and 7.5, 11k: 7.8 and 6.6, 180k: 16.4 and 14.3, 1.6M: 74 and
+        // 48)
+        const long long nvg = nv * (Co / 32);
+        const bool mid = nvg >= 64000 && nvg < 170000;
+        if (march_fits(g, Ci, Co) && groups32 && Ci == 16 && !accumulate && !mid) {
+            const long long cols = (long long)((g.W + 15) / 16) * ((g.H + 7) / 8) * g.B * (Co / 32);
+            const int n = march_planes(g, cols);
+            const long long items = cols * ((g.D + n - 1) / n);
+#define LAUNCH_PAIRS(OUT)                                                                        \
+    hipLaunchKernelGGL(k_conv_march_pairs<OUT>, dim3((unsigned)items), dim3(256), kMhLds, s, x, w, \
+                       bias, g, Co, n, alpha, act, y16, y32, ym)
+            if (ym) LAUNCH_PAIRS(kMaDz);
+            else if (y16 && y32) LAUNCH_PAIRS(kMaBoth);
+            else if (y32) LAUNCH_PAIRS(kMaF32);
+            else LAUNCH_PAIRS(kMaBf16);
+#undef LAUNCH_PAIRS
+        } else if (Ci == 16 && groups32) LAUNCH_REG(16, 2, 4);
+        else if (Ci == 32 && march_fits(g, Ci, Co) && !accumulate && groups32) {
             const long long cols = (long long)((g.W + 15) / 16) * ((g.H + 7) / 8) * g.B * (Co / 32);
             const int n = march_planes(g, cols);
             const long long items = cols * ((g.D + n - 1) / n);

@@ -1,4 +1,4 @@
-"""The convolution of 32 channels that marches along z, and that of more in
+"""The convolutions of 16 and 32 channels that march along z, and that of more in
 passes over blocks of planes, where they can go wrong: one voxel, one plane,
 ragged rows, columns and blocks, groups of outputs, batches, and the seams
 between columns and blocks of different length."""
@@ -23,6 +23,9 @@ def _data(shape, ci, co, seed):
 @pytest.mark.parametrize("shape,ci,co", [
     ((1, 1, 1, 1), 32, 32), ((1, 1, 8, 16), 32, 32), ((2, 3, 9, 17), 32, 96),
     ((3, 2, 7, 5), 32, 64), ((1, 9, 16, 33), 32, 32), ((1, 40, 20, 36), 32, 96),
+    # two taps per step
+    ((1, 1, 1, 1), 16, 32), ((1, 1, 8, 16), 16, 32), ((2, 3, 9, 17), 16, 96),
+    ((3, 2, 7, 5), 16, 64), ((1, 40, 20, 36), 16, 32),
     # blocks of one, two and four planes
     ((1, 1, 1, 1), 64, 32), ((2, 3, 9, 17), 96, 64), ((1, 40, 16, 33), 64, 64),
     ((2, 21, 25, 36), 64, 64), ((1, 66, 17, 50), 96, 32), ((1, 5, 9, 20), 128, 128)])
@@ -48,7 +51,7 @@ def test_against_the_oracle(shape, ci, co):
         assert torch.equal(torch.where(y32 > 0, y32, alpha * y32).bfloat16(), y16)
 
 
-@pytest.mark.parametrize("ci", [32, 64])
+@pytest.mark.parametrize("ci", [16, 32, 64])
 @pytest.mark.parametrize("depth", [2, 3, 5, 17, 33])
 def test_seams(depth, ci):
     """Output planes away from the cut do not depend on where columns and
