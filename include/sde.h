@@ -203,8 +203,7 @@ typedef struct {
     int refill;       /* refill when at least this many lanes of a wave are idle, 1..64 (8) */
     int jump_batch;   /* finish deferred jumps when this many lanes of a wave wait, 1..64 (8) */
     int tally_replicas; /* global tally copies, chosen per XCD and summed at the end, 1..16
-                           (0: 2 for up to 1024 histories per compute unit, 4 for up
-                           to 65536, else 8) */
+                           (0: 2 for up to 1024 histories per compute unit, else 8) */
     int claim_chunk;  /* most history indices a wave takes from the work counter at once, >= 64 (64) */
     int tile_nx, tile_ny, tile_nz;   /* LDS tally tile extent in voxels (0: none) */
     int tile_x0, tile_y0, tile_z0;   /* tile low corner in voxels */

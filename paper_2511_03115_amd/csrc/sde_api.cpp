@@ -304,14 +304,12 @@ int make_plan(const sde_beam* beam, const sde_phantom* ph, uint64_t n_histories,
     // Replicas keep hot lines in one XCD's L2, but each costs a pass over the
     // voxels to sum.  With at most one history per lane two do (2e5 on 8M
     // voxels: 1.23 ms with 2, 1.20 with 4, 1.28 with 8; 1e5 on 2M: kernel 0.91
-    // with any); to 65536 per compute unit four (1e6 on 8M: 4.72, 4.42 and 4.39;
-    // 1e6 on 12M: 4.16, 4.28 and 4.37; 2e6 on 13M: 6.76, 6.78 and 6.90);
-    // beyond, the atomics decide (2e7 on 13M: 66.4, 65.3 and 65.0).
-    const uint64_t per_cu = total / (uint64_t)std::max(1, g.n_cu);
+    // with any); with more, eight: an XCD each (1e6 in an inhomogeneous head:
+    // 5.29 with 2, 5.60 with 4, 5.01 with 8; 4e6: 19.6, 18.4 and 16.4; 2e6 of 1000
+    // spots, many lines: 6.76, 6.78 and 6.90).
     const int n_rep = L.tally_replicas ? L.tally_replicas
-                      : per_cu <= 1024 ? 2
-                      : per_cu <= 65536 ? 4
-                                        : 8;
+                      : total <= 1024ull * (uint64_t)std::max(1, g.n_cu) ? 2
+                                                                         : 8;
     if (n_rep < 1 || n_rep > 16) return fail(SDE_E_INVALID, "tally_replicas must be in 1..16");
 
     sde_plan* p = new sde_plan();

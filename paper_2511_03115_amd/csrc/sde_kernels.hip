@@ -1549,11 +1549,11 @@ __global__ void k_reset(unsigned long long* tally, size_t nvox, unsigned long lo
 // the replicas goes to replica 0, the others are left zero again (most of them
 // are: only what a beam touched is written), so that a plan's next execution
 // clears replica 0 alone.  HBM bound: the replicas and the voxel word read,
-// total and dose written, 56 B per voxel of four replicas, all replicas' loads
+// total and dose written, 88 B per voxel of eight replicas, all replicas' loads
 // in flight.  On 13M voxels under 1000 spots: eight replicas summed in a loop and
-// cleared by the reset 233 + 129 us; zeroed here, all loads in flight, 287 + 17;
-// four replicas 162 + 17 (4.9 TB/s).  Whole lines of zeros where any lane's
-// word is nonzero cost 10 % more than the lanes' own.
+// cleared by the reset 233 + 129 us; zeroed here, all loads in flight, 287 + 17.
+// Whole lines of zeros where any lane's word is nonzero cost 10 % more than the
+// lanes' own.
 template <int kRep>
 __global__ void __launch_bounds__(256) k_convert(unsigned long long* tally, int n_rep,
                                                  const uint2* vox, size_t nvox, double inv_scale,
@@ -1719,8 +1719,6 @@ hipError_t launch_convert(unsigned long long* tally, int n_rep, const uint2* vox
     };
     if (n_rep == 8)
         go(k_convert<8>);
-    else if (n_rep == 4)
-        go(k_convert<4>);
     else if (n_rep == 2)
         go(k_convert<2>);
     else

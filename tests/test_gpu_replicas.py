@@ -44,7 +44,7 @@ def test_executions_with_replicas(n_rep):
 
 @pytest.mark.parametrize("n", [1000, 263_000])
 def test_default_replicas_over_the_rule(n):
-    """Two and four by default: the tally of one."""
+    """Two and eight by default: the tally of one."""
     import torch
     from paper_2511_03115_amd import sde
     wl = configs.slab(80.0, n=n, size=33, depth=61)
