@@ -3967,8 +3967,9 @@ hipError_t conv_fwd(const uint16_t* x, const uint16_t* w, const float* bias, con
         if (Co == 16 && Ci == 48)
             return launch_rows<48, 48>(x, nullptr, w, bias, g, alpha, act, y16, y32, accumulate, s);
         bool done = true;
-        // 32 outputs, 96 as three groups of 32, or 64 as two when the bricks
-        // are too few to fill the device
+        // by columns any groups of 32 outputs (32 inputs, 64 outputs of 327k voxels:
+        // 110 us from weight slabs, 56 by columns); by bricks 32, 96 as three groups, or
+        // 64 as two when they are too few to fill the device
         const bool few = nbk < kFewBricks;
         const bool groups32 = nt == 2 || nt == 6 || (nt == 4 && few);
         // 16 inputs: by columns, but for 64k to 170k voxels and groups, where bricks
@@ -3976,8 +3977,8 @@ hipError_t conv_fwd(const uint16_t* x, const uint16_t* w, const float* bias, con
         // 13.5; 17k: 7.6 and 7.5, 11k: 7.8 and 6.6, 180k: 16.4 and 14.3, 1.6M: 74 and
         // 48)
         const long long nvg = nv * (Co / 32);
-        const bool mid = nvg >= 64000 && nvg < 170000;
-        if (march_fits(g, Ci, Co) && groups32 && Ci == 16 && !accumulate && !mid) {
+        const bool mid = groups32 && nvg >= 64000 && nvg < 170000;
+        if (march_fits(g, Ci, Co) && nt % 2 == 0 && Ci == 16 && !accumulate && !mid) {
             const long long cols = (long long)((g.W + 15) / 16) * ((g.H + 7) / 8) * g.B * (Co / 32);
             const int n = march_planes(g, cols);
             const long long items = cols * ((g.D + n - 1) / n);
@@ -3990,7 +3991,7 @@ hipError_t conv_fwd(const uint16_t* x, const uint16_t* w, const float* bias, con
             else LAUNCH_PAIRS(kMaBf16);
 #undef LAUNCH_PAIRS
         } else if (Ci == 16 && groups32) LAUNCH_REG(16, 2, 4);
-        else if (Ci == 32 && march_fits(g, Ci, Co) && !accumulate && groups32) {
+        else if (Ci == 32 && march_fits(g, Ci, Co) && !accumulate && nt % 2 == 0) {
             const long long cols = (long long)((g.W + 15) / 16) * ((g.H + 7) / 8) * g.B * (Co / 32);
             const int n = march_planes(g, cols);
             const long long items = cols * ((g.D + n - 1) / n);

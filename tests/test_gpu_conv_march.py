@@ -23,9 +23,11 @@ def _data(shape, ci, co, seed):
 @pytest.mark.parametrize("shape,ci,co", [
     ((1, 1, 1, 1), 32, 32), ((1, 1, 8, 16), 32, 32), ((2, 3, 9, 17), 32, 96),
     ((3, 2, 7, 5), 32, 64), ((1, 9, 16, 33), 32, 32), ((1, 40, 20, 36), 32, 96),
+    ((1, 5, 12, 20), 32, 128),
     # two taps per step
     ((1, 1, 1, 1), 16, 32), ((1, 1, 8, 16), 16, 32), ((2, 3, 9, 17), 16, 96),
     ((3, 2, 7, 5), 16, 64), ((1, 40, 20, 36), 16, 32),
+    ((1, 5, 12, 20), 16, 128),
     # blocks of one, two and four planes
     ((1, 1, 1, 1), 64, 32), ((2, 3, 9, 17), 96, 64), ((1, 40, 16, 33), 64, 64),
     ((2, 21, 25, 36), 64, 64), ((1, 66, 17, 50), 96, 32), ((1, 5, 9, 20), 128, 128)])
