@@ -92,3 +92,24 @@ def test_level0_concatenation(B, D, H, W):
         outs.append(out.cpu().numpy())
         net.close()
     assert np.isfinite(outs[0]).all() and np.array_equal(*outs)
+
+
+@pytest.mark.parametrize("ci,co", [(16, 32), (32, 32), (64, 64)])
+def test_fp32_output_at_any_float(ci, co):
+    """FP32 outputs and biases need no more than a float's alignment, and
+    nothing is written beside them."""
+    import torch
+    from paper_2511_03115_amd import nn
+    shape = (1, 9, 12, 20)
+    x, w, b = _data(shape, ci, co, 6)
+    xd, wd = to_bf16_dev(x), to_bf16_dev(w)
+    bd = torch.from_numpy(np.concatenate([[0.0], b]).astype(np.float32)).cuda()[1:]
+    n = int(np.prod(shape)) * co
+    want = torch.zeros(shape + (co,), dtype=torch.float32, device="cuda")
+    nn.conv3d_fwd(xd, wd, bd, act=False, out32=want)
+    for off in (1, 2, 3):
+        log(f"unaligned output ci={ci} co={co} off={off}")
+        flat = torch.zeros(n + 8, dtype=torch.float32, device="cuda")
+        nn.conv3d_fwd(xd, wd, bd, act=False, out32=flat[off:off + n].view(shape + (co,)))
+        assert torch.equal(flat[off:off + n].view(shape + (co,)), want)
+        assert not flat[:off].any() and not flat[off + n:].any()
