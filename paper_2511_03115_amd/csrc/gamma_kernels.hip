@@ -175,11 +175,17 @@ __device__ __forceinline__ double bilinear_min(double e00, double e10, double e0
 // in the octant's direction and d = |v(0) - dr|, |v(o) - dr| >= d - g . |o|,
 // and the smallest value of |o|^2 / dta^2 + max(0, d - g . |o|)^2 / norm^2 over all
 // o is d^2 / (norm^2 + |g|^2 dta^2): above 1, by 1e-9 (far beyond rounding),
-// nothing passes.  Infinite or NaN corners compare false, and the rows decide.
+// nothing passes.  With an infinite or NaN corner the slopes mean nothing (and
+// the offsets on a face towards the next cell, which dta equal to a voxel
+// reaches, are that cell's): the rows decide.
 __device__ __forceinline__ bool octant_open(const GammaArgs& A, const GammaLattice& L, Octant& O,
                                             int& ca, int& cb, int& cc) {
     const int K = A.K, KK = K * K;
     const double* v = O.v;
+    ca = cb = cc = 0;
+    const double big = ((fabs(v[0]) + fabs(v[1])) + (fabs(v[2]) + fabs(v[3]))) +
+                       ((fabs(v[4]) + fabs(v[5])) + (fabs(v[6]) + fabs(v[7])));
+    if (!__builtin_isfinite(big)) return true;
     // the box in cell coordinates: from t (the voxel's own corner) by r
     const double tx = O.ix - O.x0, ty = O.iy - O.y0, tz = O.iz - O.z0;
     const double rx = O.sx || O.ix + 1 < A.nx ? L.vx[0][2 * K] : 0.0;
@@ -199,8 +205,6 @@ __device__ __forceinline__ bool octant_open(const GammaArgs& A, const GammaLatti
     const double px = rx * fmax(0.0, -bilinear_min(x00, x10, x01, x11, ty, uy, tz, uz, sg * gx));
     const double py = ry * fmax(0.0, -bilinear_min(y00, y10, y01, y11, tx, ux, tz, uz, sg * gy));
     const double pz = rz * fmax(0.0, -bilinear_min(z00, z10, z01, z11, tx, ux, ty, uy, sg * gz));
-    const double big = fmax(fmax(fmax(fabs(v[0]), fabs(v[1])), fmax(fabs(v[2]), fabs(v[3]))),
-                            fmax(fmax(fabs(v[4]), fabs(v[5])), fmax(fabs(v[6]), fabs(v[7]))));
     const double d = fabs(d0) - 1e-12 * fmax(big, fabs(O.dr));
     if (d > 0.0) {
         if (d * d > (O.norm2 + px * px + py * py + pz * pz) * (1.0 + 1e-9)) return false;
@@ -216,7 +220,6 @@ __device__ __forceinline__ bool octant_open(const GammaArgs& A, const GammaLatti
     const double qy = ry * fmax(0.0, -sg * gy * (hz ? (hx ? y11 : y01) : (hx ? y10 : y00)));
     const double qz = rz * fmax(0.0, -sg * gz * (hy ? (hx ? z11 : z01) : (hx ? z10 : z00)));
     const double den = O.norm2 + qx * qx + qy * qy + qz * qz;
-    ca = cb = cc = 0;
     if (d * d <= den) {   // then the minimum lies within dta
         const double k = K * fabs(d0) / den, ex = qx * k, ey = qy * k, ez = qz * k;
         if (ex <= K && ey <= K && ez <= K) {   // (not NaN)
