@@ -182,10 +182,6 @@ __device__ __forceinline__ bool octant_open(const GammaArgs& A, const GammaLatti
                                             int& ca, int& cb, int& cc) {
     const int K = A.K, KK = K * K;
     const double* v = O.v;
-    ca = cb = cc = 0;
-    const double big = ((fabs(v[0]) + fabs(v[1])) + (fabs(v[2]) + fabs(v[3]))) +
-                       ((fabs(v[4]) + fabs(v[5])) + (fabs(v[6]) + fabs(v[7])));
-    if (!__builtin_isfinite(big)) return true;
     // the box in cell coordinates: from t (the voxel's own corner) by r
     const double tx = O.ix - O.x0, ty = O.iy - O.y0, tz = O.iz - O.z0;
     const double rx = O.sx || O.ix + 1 < A.nx ? L.vx[0][2 * K] : 0.0;
@@ -205,7 +201,9 @@ __device__ __forceinline__ bool octant_open(const GammaArgs& A, const GammaLatti
     const double px = rx * fmax(0.0, -bilinear_min(x00, x10, x01, x11, ty, uy, tz, uz, sg * gx));
     const double py = ry * fmax(0.0, -bilinear_min(y00, y10, y01, y11, tx, ux, tz, uz, sg * gy));
     const double pz = rz * fmax(0.0, -bilinear_min(z00, z10, z01, z11, tx, ux, ty, uy, sg * gz));
-    const double d = fabs(d0) - 1e-12 * fmax(big, fabs(O.dr));
+    const double big = ((fabs(v[0]) + fabs(v[1])) + (fabs(v[2]) + fabs(v[3]))) +
+                       ((fabs(v[4]) + fabs(v[5])) + (fabs(v[6]) + fabs(v[7])));
+    const double d = fabs(d0) - 1e-12 * (big + fabs(O.dr));   // no more than 0, or NaN, beside them
     if (d > 0.0) {
         if (d * d > (O.norm2 + px * px + py * py + pz * pz) * (1.0 + 1e-9)) return false;
         const double near = d - (px + py + pz);   // the octant's closest approach to dr
@@ -220,6 +218,7 @@ __device__ __forceinline__ bool octant_open(const GammaArgs& A, const GammaLatti
     const double qy = ry * fmax(0.0, -sg * gy * (hz ? (hx ? y11 : y01) : (hx ? y10 : y00)));
     const double qz = rz * fmax(0.0, -sg * gz * (hy ? (hx ? z11 : z01) : (hx ? z10 : z00)));
     const double den = O.norm2 + qx * qx + qy * qy + qz * qz;
+    ca = cb = cc = 0;
     if (d * d <= den) {   // then the minimum lies within dta
         const double k = K * fabs(d0) / den, ex = qx * k, ey = qy * k, ez = qz * k;
         if (ex <= K && ey <= K && ez <= K) {   // (not NaN)
@@ -423,11 +422,15 @@ __global__ void __launch_bounds__(256) k_gamma_screen(GammaArgs A) {
 // lanes each, one octant a lane: most octants are closed by the bound of
 // octant_open or decided by the one offset it names, in a few hundred
 // operations with all lanes busy.  The octants left open (a band around the
-// boundary) are then searched one after another by the whole wave, a row of
-// offsets per lane.  Bound by FP64 issue.  One thread walking all of a voxel's
+// boundary; all of them where dta is above a voxel) are then searched one after
+// another by the whole wave, a row of offsets per lane.  kOwn: before that, while
+// their rows are no more than the whole wave would take for the open ones, each
+// lane walks its own octant, outward from the voxel, until one of its voxel's
+// has passed.  Bound by FP64 issue.  One thread walking all of a voxel's
 // rows took 2876 us for a plan map's list (256 x 256 x 200, 82 % passing), its
 // waves waiting for their longest lanes, against 407 us so; on 40 x 40 x 150,
 // where one walk's latency is the time, 663 against 31 us.
+template <bool kOwn>
 __global__ void __launch_bounds__(256) k_gamma_search(GammaArgs A) {
     const unsigned nl = (unsigned)A.buf[0];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, sub = lane & 7;
@@ -491,6 +494,30 @@ __global__ void __launch_bounds__(256) k_gamma_search(GammaArgs A) {
             return g;
         };
         drop_passed();
+        // rows (|a| - sx, |b| - sy) on a square; the whole wave takes an octant's 64
+        // at a time, and about two rows' time to hand it round
+        if (kOwn && todo) {
+            int nm = (todo >> lane) & 1 ? O.nmax : 0;
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) nm = max(nm, __shfl_xor(nm, o));
+            const int side = min((int)sqrtf((float)nm + 0.5f), K) + 1, rows = side * side;
+            for (int r = 0, q = 0, u = 0;
+                 r < rows && rows - r <= __popcll(todo) * (2 + (rows + 63) / 64); ++r) {
+                bool p = false;
+                if (((todo >> lane) & 1) && q + O.sx <= K && u + O.sy <= K)
+                    p = row_passes(A, L, O, O.sx ? -(q + 1) : q, O.sy ? -(u + 1) : u);
+                const unsigned long long hit = __ballot(p);
+                if (hit) {
+                    done |= hit;
+                    drop_passed();
+                }
+                if (++u == side) {
+                    u = 0;
+                    ++q;
+                }
+                if (r + 1 == rows) todo = 0;
+            }
+        }
         while (todo) {
             const int l = __builtin_ctzll(todo);
             todo &= todo - 1;
@@ -510,7 +537,6 @@ __global__ void __launch_bounds__(256) k_gamma_search(GammaArgs A) {
             U.inv_n2 = lane_value(O.inv_n2, l);
 #pragma unroll
             for (int j = 0; j < 8; ++j) U.v[j] = lane_value(O.v[j], l);
-            // rows (|a| - sx, |b| - sy) on a square of side n, 64 at a time
             const int n = min((int)sqrtf((float)U.nmax + 0.5f), K) + 1;
             const float inv = 1.0f / (float)n;
             bool hit = false;
@@ -588,6 +614,12 @@ hipError_t launch_gamma(const double* ref, const double* ev, int nx, int ny, int
     const size_t nvox = (size_t)nx * ny * nz;
     GammaArgs A{ref, ev, nx, ny, nz, interp, dta / interp, dta, dx, dy, dz, dd, thresh, inv_dta2,
                 local, use_bound, 1.0 / nx, 1.0 / ny, 0, 0, max_blocks(nvox), buf, list};
+    // Above a voxel every octant is open, and mostly passes near the voxel; with
+    // few offsets per octant the whole wave is mostly idle (120 x 120 x 120 voxels
+    // of 1 mm, own octants first against the whole wave alone: dta 3 mm, 2 offsets
+    // per dta 793 and 6658 us, 10 790 and 4268; dta 0.5 mm, 2 offsets 693 and 1765,
+    // 3 946 and 1400; 4 1390 and 1260, 10 1665 and 1555)
+    const bool own = !use_bound || interp <= 3;
     // a grid beyond the list's capacity goes in passes of cap voxels, so that
     // the list cannot overflow
     for (size_t v0 = 0; v0 < nvox; v0 += cap) {
@@ -599,7 +631,8 @@ hipError_t launch_gamma(const double* ref, const double* ev, int nx, int ny, int
         if ((e = hipGetLastError()) != hipSuccess) return e;
         // the list's length is on the device: at most 32 voxels a workgroup,
         // a stride over the list beyond 2048 workgroups
-        hipLaunchKernelGGL(k_gamma_search, dim3(blocks_for(A.nv, 32, 2048)), dim3(256), 0, s, A);
+        const auto search = own ? k_gamma_search<true> : k_gamma_search<false>;
+        hipLaunchKernelGGL(search, dim3(blocks_for(A.nv, 32, 2048)), dim3(256), 0, s, A);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     return hipSuccess;
