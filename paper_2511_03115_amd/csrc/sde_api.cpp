@@ -234,7 +234,7 @@ sde_launch default_launch(const sde_beam* beam, const sde_phantom* ph,
         int x0[2];
         for (int a = 0; a < 2; ++a) {
             const double v = std::floor((c[a] / wsum - ph->origin_cm[a]) / d[a]) - t / 2;
-            x0[a] = (int)std::min(std::max(v, 0.0), (double)(n[a] - t));
+            x0[a] = v > 0.0 ? (int)std::min(v, (double)(n[a] - t)) : 0;   // (a NaN origin: 0)
         }
         L.tile_nx = L.tile_ny = t;
         L.tile_nz = fit;
