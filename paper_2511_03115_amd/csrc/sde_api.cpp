@@ -130,7 +130,8 @@ struct sde_plan {
     int n_rep = 1;
     double scale = 1.0;
     double voxel_cm3 = 0;
-    bool dirty = false;   // an execution failed half-way: every reset clears all replicas
+    bool dirty = false;   // an execution failed half-way: the next one clears all replicas
+    bool graph_clears_all = false;   // the graph was recorded for such an execution
     hipGraph_t graph = nullptr;
     hipGraphExec_t gexec = nullptr;
     double* graph_dose = nullptr;
@@ -155,14 +156,15 @@ void plan_free(sde_plan* p) {
 // (dose_out may be NULL); with timing, HIP events bracket the transport launch.
 // Replicas 1.. are zero between executions (zeroed when the plan is made, left
 // so by the conversion), so the reset clears replica 0 alone: 64 -> 8 B per
-// voxel, 121 -> 20 us on 12M voxels.  cleared: nothing has run since the plan
-// was made, and the reset is left out.
+// voxel, 121 -> 20 us on 12M voxels.  After an execution that failed half-way
+// (dirty) the next one clears them all.  cleared: nothing has run since the
+// plan was made, and the reset is left out.
 int plan_enqueue(sde_plan* p, double* dose_out, hipStream_t s, bool timing = false,
                  bool cleared = false) {
     if (!cleared)
         HIP_TRY(launch_reset(p->tally, p->dirty ? p->nvox * p->n_rep : p->nvox, p->ledger,
                              p->counter, s));
-    const bool dirty = p->dirty;
+    bool dirty = p->dirty;
     p->dirty = true;   // until the conversion is enqueued
     if (timing) {
         if (!p->ev0) HIP_TRY(hipEventCreate(&p->ev0));
@@ -176,6 +178,10 @@ int plan_enqueue(sde_plan* p, double* dose_out, hipStream_t s, bool timing = fal
     }
     HIP_TRY(launch_convert(p->tally, p->n_rep, p->vox, p->nvox, 1.0 / p->scale, p->voxel_cm3,
                            dose_out, p->ledger, s));
+    if (dirty) {   // cleared now, unless the stream only records
+        hipStreamCaptureStatus st = hipStreamCaptureStatusActive;
+        dirty = hipStreamIsCapturing(s, &st) != hipSuccess || st != hipStreamCaptureStatusNone;
+    }
     p->dirty = dirty;
     return SDE_OK;
 }
@@ -711,13 +717,17 @@ int sde_plan_execute(sde_plan* p, double* dose_out, int use_graph) {
         if (!g.own) HIP_TRY(hipStreamCreate(&g.own));
         s = g.own;
     }
-    if (!p->gexec || p->dirty || p->graph_dose != dose_out || p->graph_stream != s) {
+    if (!p->gexec || p->dirty || p->graph_clears_all || p->graph_dose != dose_out ||
+        p->graph_stream != s) {
         if (p->gexec) (void)hipGraphExecDestroy(p->gexec);
         if (p->graph) (void)hipGraphDestroy(p->graph);
         p->gexec = nullptr;
         p->graph = nullptr;
         HIP_TRY(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
+        const bool dirty = p->dirty;
         const int rc = plan_enqueue(p, dose_out, s);
+        p->dirty = dirty;   // nothing has run
+        p->graph_clears_all = dirty;
         hipGraph_t gr = nullptr;
         const hipError_t e = hipStreamEndCapture(s, &gr);
         if (rc != SDE_OK) {
@@ -731,6 +741,7 @@ int sde_plan_execute(sde_plan* p, double* dose_out, int use_graph) {
         p->graph_stream = s;
     }
     HIP_TRY(hipGraphLaunch(p->gexec, s));
+    p->dirty = false;   // a graph recorded while it was set clears all replicas
     if (s != cur_stream()) HIP_TRY(hipStreamSynchronize(s));
     return SDE_OK;
 }

@@ -16,6 +16,7 @@ static int failures = 0;
 static size_t last_reset = 0;         // voxel words cleared by the last reset
 static int fail_transport = 0;        // fail the next launches of the transport
 static int instantiated = 0;          // graphs
+static int launched = 0;
 static bool capturing = false;
 static sde::KParams last_params;
 
@@ -65,7 +66,10 @@ hipError_t hipGraphInstantiate(hipGraphExec_t* e, hipGraph_t, hipGraphNode_t*, c
     *e = reinterpret_cast<hipGraphExec_t>(8);
     return hipSuccess;
 }
-hipError_t hipGraphLaunch(hipGraphExec_t, hipStream_t) { return hipSuccess; }
+hipError_t hipGraphLaunch(hipGraphExec_t, hipStream_t) {
+    ++launched;
+    return hipSuccess;
+}
 hipError_t hipGraphDestroy(hipGraph_t) { return hipSuccess; }
 hipError_t hipGraphExecDestroy(hipGraphExec_t) { return hipSuccess; }
 hipError_t hipEventCreate(hipEvent_t* e) {
@@ -169,6 +173,48 @@ int main(int argc, char** argv) {
             check(what, rc == SDE_OK);
             sde_plan_destroy(p);
         }
+    // tally replicas: an execution clears the first one; after one that failed
+    // half-way the next clears all of them, and no later one does
+    sde_launch L{};
+    L.tally_replicas = 4;
+    for (const int graph : {0, 1}) {
+        std::printf("graph %d\n", graph);
+        p = nullptr;
+        check("plan", sde_plan_create(&beam, &ph, 0, 1, &L, &p) == SDE_OK);
+        check("executes", sde_plan_execute(p, dose, graph) == SDE_OK && last_reset == nvox);
+        fail_transport = 1;
+        check("an execution fails", sde_plan_execute(p, dose, 0) != SDE_OK);
+        last_reset = 0;
+        check("the next clears every replica",
+              sde_plan_execute(p, dose, graph) == SDE_OK && last_reset == 4 * nvox);
+        check("the one after the first alone",
+              sde_plan_execute(p, dose, graph) == SDE_OK && last_reset == nvox);
+        const int made = instantiated, ran = launched;
+        check("and goes on", sde_plan_execute(p, dose, graph) == SDE_OK &&
+                                 sde_plan_execute(p, dose, 1 - graph) == SDE_OK &&
+                                 last_reset == nvox);
+        check("with the graph it has", graph ? instantiated == made && launched == ran + 1
+                                             : instantiated <= made + 1);
+        sde_plan_destroy(p);
+    }
+    // recording runs nothing: one that fails leaves the replicas as they were
+    p = nullptr;
+    check("plan", sde_plan_create(&beam, &ph, 0, 1, &L, &p) == SDE_OK);
+    fail_transport = 1;
+    check("recording fails", sde_plan_execute(p, dose, 1) != SDE_OK);
+    check("the next execution clears the first replica",
+          sde_plan_execute(p, dose, 0) == SDE_OK && last_reset == nvox);
+    fail_transport = 1;
+    check("an execution fails", sde_plan_execute(p, dose, 0) != SDE_OK);
+    // a caller's own recording of an execution clears all, and so does the next
+    capturing = true;
+    check("recorded by the caller",
+          sde_plan_execute(p, dose, 0) == SDE_OK && last_reset == 4 * nvox);
+    capturing = false;
+    last_reset = 0;
+    check("and run", sde_plan_execute(p, dose, 0) == SDE_OK && last_reset == 4 * nvox);
+    check("then the first alone", sde_plan_execute(p, dose, 0) == SDE_OK && last_reset == nvox);
+    sde_plan_destroy(p);
     std::printf("done: %d failures\n", failures);
     return failures ? 1 : 0;
 }

@@ -1,6 +1,7 @@
 """The plans' host logic of the C ABI on the CPU (tests/host/plan_main.cpp): the
-launch chosen for a caller who names none, with the HIP runtime and the kernel
-launchers replaced by stand-ins."""
+launch chosen for a caller who names none, and what an execution clears after one
+that failed, with the HIP runtime and the kernel launchers replaced by
+stand-ins."""
 
 import os
 import shutil
