@@ -1585,7 +1585,6 @@ k_conv_march(const uint16_t* __restrict__ x, const uint16_t* __restrict__ w,
     r /= nby;
     const int z0 = (r % nbz) * n, b = r / nbz;
     const int z1 = min(z0 + n, g.D);
-    const int zs = max(z0 - 1, 0);   // input planes zs..z1
     const __amdgpu_buffer_rsrc_t xr = rsrc16(x, g.nvox() * 32);
     const __amdgpu_buffer_rsrc_t wr = rsrc16(w, (long long)Co * K);
 
@@ -1608,7 +1607,7 @@ k_conv_march(const uint16_t* __restrict__ x, const uint16_t* __restrict__ w,
     }
     uint4 rx[NL];
     auto load_plane = [&](int z) {
-        const unsigned off = z <= z1 && z < g.D ? (unsigned)(z * plane) : (unsigned)kOob;
+        const unsigned off = z >= 0 && z <= z1 && z < g.D ? (unsigned)(z * plane) : (unsigned)kOob;
 #pragma unroll
         for (int k = 0; k < NL; ++k)
             rx[k] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(
@@ -1621,14 +1620,14 @@ k_conv_march(const uint16_t* __restrict__ x, const uint16_t* __restrict__ w,
                 *reinterpret_cast<uint4*>(hx + buf * kMaVox * kMaRow + lo[k]) = rx[k];
     };
 
-    f32x4 acc[3][R];   // output plane zs + i in acc[i % 3]
+    f32x4 acc[3][R];   // output plane z0 - 1 + i in acc[i % 3]
 #pragma unroll
     for (int t = 0; t < 3; ++t)
 #pragma unroll
         for (int m = 0; m < R; ++m) acc[t][m] = f32x4{0.f, 0.f, 0.f, 0.f};
     const int fb = ((wave >> 1) * R * 18 + (lane & 15)) * kMaRow + q * 8;
-    // the products of input plane zs + i, I = i % 3, with the output planes of
-    // the mask Z (bit tz: plane zs + i + 1 - tz)
+    // the products of input plane z = z0 - 1 + i, I = i % 3, with the output planes
+    // of the mask Z (bit tz: plane z + 1 - tz)
     auto products = [&](auto idx, auto taps) {
         constexpr int I = decltype(idx)::value, Z = decltype(taps)::value;
         // a row's fragments are read during the previous row's products
@@ -1688,7 +1687,7 @@ k_conv_march(const uint16_t* __restrict__ x, const uint16_t* __restrict__ w,
     auto emit = [&](int z, const f32x4 (&c)[R]) {
         store_rows<OUT, R>(c, bq, act, alpha, ymk, rsrc_plane(y16, z, 2), rsrc_plane(y32, z, 4), yo);
     };
-    // input plane z = zs + i, I = i % 3, from buffer I; the next plane goes to
+    // input plane z = z0 - 1 + i, I = i % 3, from buffer I; the next plane goes to
     // the next buffer (last read two steps ago), the one after is loaded
     auto step = [&](int z, auto idx) {
         constexpr int I = decltype(idx)::value;
@@ -1706,10 +1705,10 @@ k_conv_march(const uint16_t* __restrict__ x, const uint16_t* __restrict__ w,
             products(idx, std::integral_constant<int, 7>{});
         emit(z - 1, acc[(I + 2) % 3]);
     };
-    load_plane(zs);
+    load_plane(z0 - 1);
     store_lds(0);
-    load_plane(zs + 1);
-    for (int z = zs;;) {
+    load_plane(z0);
+    for (int z = z0 - 1;;) {
         step(z, std::integral_constant<int, 0>{});
         if (++z > z1) break;
         step(z, std::integral_constant<int, 1>{});
