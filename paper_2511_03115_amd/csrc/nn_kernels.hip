@@ -3235,6 +3235,7 @@ k_wgrad_cols(const uint16_t* __restrict__ dz, const uint16_t* __restrict__ x,
     // part[co block][c][ci block][t][lane][4]: the accumulators as they lie
     f32x4* const out = reinterpret_cast<f32x4*>(part) +
                        (((size_t)cob * used + c) * nci + cib) * 27 * 64;
+    bool nans = false;
 #pragma unroll
     for (int tz = 0; tz < 3; ++tz) {
         __syncthreads();
@@ -3246,7 +3247,60 @@ k_wgrad_cols(const uint16_t* __restrict__ dz, const uint16_t* __restrict__ x,
 #pragma unroll
             for (int w = 1; w < 8; ++w) s += red[w * 9 * 64 + i];
             out[tz * 9 * 64 + i] = s;
+            const float any = (s[0] + s[1]) + (s[2] + s[3]);
+            nans |= any != any;
         }
+    }
+    if (__any(nans)) {
+        // A NaN may come from a column's rim, where the output gradients are
+        // zeros that stand for none (0 x Inf): the wave forms such sums again,
+        // product by product, unless a few already meet one.  Finite and infinite
+        // sums cannot come from there.  2.1M voxels, 16 -> 16: 40 us without NaN,
+        // 3.5 ms with one NaN voxel, 1.0 ms with nothing else.
+        float* const f = reinterpret_cast<float*>(out);
+        const int first = 4 * c * cpw, last = min(first + 4 * cpw, ncol), nu = n * RY * 16;
+        // voxel u of a column's, tap and channels of element (i, j)
+        auto product = [&](int col, int u, int i, int j) {
+            int r = col;
+            const int xx = (r % nbx) * 16 + (u & 15);
+            r /= nbx;
+            const int yy = (r % nby) * RY + (u >> 4) % RY;
+            r /= nby;
+            const int zz = (r % nbz) * n + u / (16 * RY), b = r / nbz;
+            const int t = i >> 6, l = i & 63, ci = ci0 + (l & 15), co = co0 + (l >> 4) * 4 + j;
+            if (xx >= g.W || yy >= g.H || zz >= g.D) return 0.0;
+            const int xi = xx + t % 3 - 1, yi = yy + t / 3 % 3 - 1, zi = zz + t / 9 - 1;
+            const bool in = (unsigned)xi < (unsigned)g.W && (unsigned)yi < (unsigned)g.H &&
+                            (unsigned)zi < (unsigned)g.D;
+            const long long v = ((b * (long long)(g.D >> low) + (zi >> low)) * (g.H >> low) +
+                                 (yi >> low)) * (g.W >> low) + (xi >> low);
+            const long long o = ((b * (long long)g.D + zz) * g.H + yy) * g.W + xx;
+            const uint16_t* const src = lowsrc ? xl + (ci - Cs) : x + ci;
+            return (double)bf2f(dz[o * Co + co]) * (in ? bf2f(src[v * (lowsrc ? Cu : Cs)]) : 0.0f);
+        };
+        for (int e = t8; e < 9 * 64; e += 512)   // (whole waves)
+            for (int k = 0; k < 12; ++k) {
+                const int i = (k >> 2) * 9 * 64 + e, j = k & 3;
+                bool open = f[i * 4 + j] != f[i * 4 + j];
+                double sum = 0.0;
+                for (int u = nu / 2; open && u < nu && sum == sum; u += nu / 8)
+                    sum += product(first, u, i, j);
+                open &= sum == sum;
+                for (unsigned long long m = __ballot(open); m; m &= m - 1) {
+                    const int l = __builtin_ctzll(m);
+                    sum = 0.0;
+                    for (int col = first, u = lane; col < last && !__any(sum != sum);) {
+                        sum += product(col, u, i - lane + l, j);
+                        if ((u += 64) >= nu) {
+                            u = lane;
+                            ++col;
+                        }
+                    }
+#pragma unroll
+                    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+                    if (lane == l) f[i * 4 + j] = (float)sum;
+                }
+            }
     }
     if (cib == 0) {   // every column of the product with ones is the sum
         __syncthreads();
