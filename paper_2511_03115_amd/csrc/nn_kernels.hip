@@ -15,6 +15,7 @@
 #include <type_traits>
 
 #include "nn_internal.hpp"
+#include "nn_plan.hpp"
 
 namespace sde {
 namespace nn {
@@ -54,11 +55,6 @@ __device__ __forceinline__ uint4 ld16(__amdgpu_buffer_rsrc_t r, int off, bool ok
         __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, ok ? off : 0, 0, 0));
     return ok ? v : make_uint4(0, 0, 0, 0);
 }
-
-struct Geo {
-    int B, D, H, W;
-    __host__ __device__ __forceinline__ long long nvox() const { return (long long)B * D * H * W; }
-};
 
 // ---------------------------------------------------------------------------
 // conv3d 3x3x3, zero padding 1, stride 1: y[v][co] = act(bias[co] +
@@ -195,7 +191,6 @@ constexpr int kHVox = (kHZ + 2) * (kHY + 2) * (kHX + 2);
 
 // Brick of the register, row-reuse and channel-pass kernels below: 4 x 4 x
 // 16 output voxels, so a 16-voxel matrix row is one run along x.
-constexpr int kRZ = 4, kRY = 4, kRX = 16;
 constexpr int kRVox = (kRZ + 2) * (kRY + 2) * (kRX + 2);
 
 // Elements per voxel slot of the row-reuse kernel's brick in LDS.  Its
@@ -1255,8 +1250,8 @@ __global__ void __launch_bounds__(256) k_conv_in(const uint32_t* __restrict__ x2
 // from L2 kept the vector-memory queue full).  Channels [0, cs) come from x
 // (cs per voxel) and [cs, Ci) from the half-size level xl,
 // nearest-neighbour upsampled (the decoder's concatenation; cs = Ci for a
-// plain input).  K order: pass, tap, channel.  For what k_conv_wide's 32-bit
-// offsets do not reach.
+// plain input).  K order: pass, tap, channel.  For volumes of few rows or planes
+// (plan_wide), and for what k_conv_wide's 32-bit offsets do not reach.
 // ---------------------------------------------------------------------------
 template <int NT, int CH, int OCC = 2>
 __global__ void __launch_bounds__(256, OCC) k_conv_fwd_pass(const uint16_t* __restrict__ x,
@@ -3951,20 +3946,30 @@ hipError_t launch_wide(const uint16_t* x, const uint16_t* xl, const uint16_t* w,
     return hipGetLastError();
 }
 
-// Output planes per block of k_conv_wide: the fewest of 1, 2 and 4 that leave
-// at most one workgroup per CU, else 4 (32 x 16 x 16 x 4 voxels, 64 -> 64:
-// 128 workgroups of 4 planes 18.7 us, 256 of 2 14.5, 512 of 1 19.4; 16 x 8 x 8 x
-// 4, 128 -> 128: 27.8, 20.5 and, 256 of 1, 17.2; 60 x 40 x 24, 64 -> 64: 300 of 4
-// 29.8, 31.3 and 42.5).
+// The channel-pass convolution: k_conv_wide, or k_conv_fwd_pass by bricks where
+// that is the faster or the offsets need it (there 64 outputs at once on
+// many bricks).
 hipError_t conv_wide(const uint16_t* x, const uint16_t* xl, const uint16_t* w, const float* bias,
                      const Geo& g, int Ci, int cs, int Co, float alpha, int act, uint16_t* y16,
-                     float* y32, const uint16_t* ym, hipStream_t s) {
-    const long long cols = (long long)((g.W + 15) / 16) * ((g.H + 7) / 8) * g.B * (Co / 32);
-    if (cols * g.D <= 256)
-        return launch_wide<1>(x, xl, w, bias, g, Ci, cs, Co, alpha, act, y16, y32, ym, s);
-    if (cols * ((g.D + 1) / 2) <= 256)
-        return launch_wide<2>(x, xl, w, bias, g, Ci, cs, Co, alpha, act, y16, y32, ym, s);
-    return launch_wide<4>(x, xl, w, bias, g, Ci, cs, Co, alpha, act, y16, y32, ym, s);
+                     float* y32, int accumulate, const uint16_t* ym, hipStream_t s) {
+    const bool fits = wide_fits(g, Ci, cs, Co) && !accumulate;
+    switch (fits ? plan_wide(g, Co).planes : 0) {
+        case 1:
+            return launch_wide<1>(x, xl, w, bias, g, Ci, cs, Co, alpha, act, y16, y32, ym, s);
+        case 2:
+            return launch_wide<2>(x, xl, w, bias, g, Ci, cs, Co, alpha, act, y16, y32, ym, s);
+        case 4:
+            return launch_wide<4>(x, xl, w, bias, g, Ci, cs, Co, alpha, act, y16, y32, ym, s);
+    }
+    const unsigned nbk = (unsigned)bricks_of(g);
+    if (Co == 64 && nbk >= kFewBricks)
+        hipLaunchKernelGGL((k_conv_fwd_pass<4, 2>), dim3(nbk), dim3(256), pass_lds_bytes(4, 2), s, x,
+                           xl, w, bias, g, Ci, cs, Co, alpha, act, y16, y32, accumulate, ym);
+    else
+        hipLaunchKernelGGL((k_conv_fwd_pass<2, 2>), dim3(nbk, Co / 32), dim3(256),
+                           pass_lds_bytes(2, 2), s, x, xl, w, bias, g, Ci, cs, Co, alpha, act, y16,
+                           y32, accumulate, ym);
+    return hipGetLastError();
 }
 }  // namespace
 
@@ -4063,22 +4068,9 @@ hipError_t conv_fwd(const uint16_t* x, const uint16_t* w, const float* bias, con
     }
     const bool few = (long long)((g.W + kRX - 1) / kRX) * ((g.H + kRY - 1) / kRY) *
                          ((g.D + kRZ - 1) / kRZ) * g.B < kFewBricks;
-    if (Ci % 32 == 0 && Ci >= 64 && (nt == 2 || nt == 4 || (nt % 2 == 0 && few))) {
-        if (wide_fits(g, Ci, Ci, Co) && !accumulate)
-            return conv_wide(x, nullptr, w, bias, g, Ci, Ci, Co, alpha, act, y16, y32, ym, s);
-        // wide input, channel passes (on few bricks in groups of 32 outputs)
-        const long long nbk = (long long)((g.W + kRX - 1) / kRX) * ((g.H + kRY - 1) / kRY) *
-                              ((g.D + kRZ - 1) / kRZ) * g.B;
-        if (nt == 2 || few)
-            hipLaunchKernelGGL((k_conv_fwd_pass<2, 2>), dim3((unsigned)nbk, nt / 2), dim3(256),
-                               pass_lds_bytes(2, 2), s, x, nullptr, w, bias, g, Ci, Ci, Co, alpha,
-                               act, y16, y32, accumulate, ym);
-        else
-            hipLaunchKernelGGL((k_conv_fwd_pass<4, 2>), dim3((unsigned)nbk), dim3(256),
-                               pass_lds_bytes(4, 2), s, x, nullptr, w, bias, g, Ci, Ci, Co, alpha,
-                               act, y16, y32, accumulate, ym);
-        return hipGetLastError();
-    }
+    // (wide input: channel passes)
+    if (Ci % 32 == 0 && Ci >= 64 && (nt == 2 || nt == 4 || (nt % 2 == 0 && few)))
+        return conv_wide(x, nullptr, w, bias, g, Ci, Ci, Co, alpha, act, y16, y32, accumulate, ym, s);
     if (nt <= 2 && Ci <= 48) {   // few channels: input brick with halo in LDS
         const size_t lds_h =
             ((size_t)kHVox * (Ci + 8) + (size_t)nt * 16 * kSlabRow) * sizeof(uint16_t);
@@ -4131,22 +4123,9 @@ hipError_t conv_cat_fwd(const uint16_t* skip, const uint16_t* low, const uint16_
     Geo g{dims[0], dims[1], dims[2], dims[3]};
     if (!conv_cat_fwd_supported(Cs, Cu, Co, g.nvox()) || (g.D | g.H | g.W) & 1 || !y16)
         return hipErrorInvalidValue;
-    const long long nbk = (long long)((g.W + kRX - 1) / kRX) * ((g.H + kRY - 1) / kRY) *
-                          ((g.D + kRZ - 1) / kRZ) * g.B;
-    if (Co == 32 || Co == 64) {
-        if (wide_fits(g, Cs + Cu, Cs, Co))
-            return conv_wide(skip, low, w, bias, g, Cs + Cu, Cs, Co, alpha, act, y16, nullptr,
-                             nullptr, s);
-        if (Co == 32 || nbk < kFewBricks)   // 64 outputs on few bricks: two groups of 32
-            hipLaunchKernelGGL((k_conv_fwd_pass<2, 2>), dim3((unsigned)nbk, Co / 32), dim3(256),
-                               pass_lds_bytes(2, 2), s, skip, low, w, bias, g, Cs + Cu, Cs, Co,
-                               alpha, act, y16, nullptr, 0, nullptr);
-        else
-            hipLaunchKernelGGL((k_conv_fwd_pass<4, 2>), dim3((unsigned)nbk), dim3(256),
-                               pass_lds_bytes(4, 2), s, skip, low, w, bias, g, Cs + Cu, Cs, Co,
-                               alpha, act, y16, nullptr, 0, nullptr);
-        return hipGetLastError();
-    }
+    if (Co == 32 || Co == 64)
+        return conv_wide(skip, low, w, bias, g, Cs + Cu, Cs, Co, alpha, act, y16, nullptr, 0,
+                         nullptr, s);
     if (g.nvox() * 32 <= kOob) {
         static const hipError_t attr = hipFuncSetAttribute(
             (const void*)k_conv_cat16, hipFuncAttributeMaxDynamicSharedMemorySize, kCatLds);
