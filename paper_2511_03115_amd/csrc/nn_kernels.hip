@@ -316,9 +316,9 @@ __global__ void __launch_bounds__(256) k_conv_fwd_halo(const uint16_t* __restric
 
 // ---------------------------------------------------------------------------
 // The halo-brick convolution with the input channel count fixed at compile
-// time, for 16 input channels and groups of 32 outputs (16 outputs take the
-// row-reuse kernel below, 32 inputs the one that marches along z; a K step
-// here is two taps, which may lie in different planes): the B fragments
+// time, for 16 or 32 input channels and groups of 32 outputs where columns that
+// march along z are not the faster (route_few; 16 outputs take the row-reuse
+// kernel below): the B fragments
 // (weights) of the K steps live in
 // registers, read from memory in chunks of CH steps, the next chunk in
 // flight while the current one feeds the matrix cores, and the whole
@@ -3813,11 +3813,8 @@ inline int blocks_for(long long n, int bs = 256, int cap = 16384) {
 }
 
 // Output planes per column (a multiple of `multiple`, which divides D) of
-// k_conv_march, and of k_conv_march16: a workgroup's time is about that
-// of 4 planes for its start and end, and n + 2 planes, 1.6 times as long with
-// two workgroups on a CU (64 x 32 x 32 x 4 voxels, 32 -> 32: n = 8, 256
-// workgroups 20.2 us, n = 6, 352: 24.3, n = 4, 512: 20.9; 50 x 24 x 40 x 2:
-// n = 4, 234 workgroups 12.7, n = 2, 450: 13.9).
+// k_conv_march16: a workgroup's time is about that of n + 2 planes, 1.6 times as
+// long with two workgroups on a CU.
 int march_planes(const Geo& g, long long cols, int multiple = 1) {
     long long best = 1LL << 60;
     int pick = g.D;
@@ -3979,9 +3976,8 @@ bool conv_dz_wide_supported(int Ci, int Co, const int* dims) {
     const bool few = (long long)((g.W + kRX - 1) / kRX) * ((g.H + kRY - 1) / kRY) *
                          ((g.D + kRZ - 1) / kRZ) * g.B < kFewBricks;
     if (Co == 16) return false;
-    // the register kernel or the channel-pass kernel takes it (as conv_fwd routes)
-    if (((Ci == 16 && g.nvox() * std::max(Ci, Co) * 2 < (1LL << 31)) ||
-         (Ci == 32 && march_fits(g, Ci, Co))) &&
+    // by columns or bricks, or in channel passes (as conv_fwd routes)
+    if ((Ci == 16 || Ci == 32) && g.nvox() * std::max(Ci, Co) * 2 < (1LL << 31) &&
         (nt == 2 || nt == 6 || (nt == 4 && few)))
         return true;
     return Ci % 32 == 0 && Ci >= 64 && (nt == 2 || nt == 4 || (nt % 2 == 0 && few));
@@ -4024,47 +4020,37 @@ hipError_t conv_fwd(const uint16_t* x, const uint16_t* w, const float* bias, con
             return launch_rows<32, 32>(x, nullptr, w, bias, g, alpha, act, y16, y32, accumulate, s);
         if (Co == 16 && Ci == 48)
             return launch_rows<48, 48>(x, nullptr, w, bias, g, alpha, act, y16, y32, accumulate, s);
-        bool done = true;
-        // by columns any groups of 32 outputs (32 inputs, 64 outputs of 327k voxels:
-        // 110 us from weight slabs, 56 by columns); by bricks 32, 96 as three groups, or
-        // 64 as two when they are too few to fill the device
-        const bool few = nbk < kFewBricks;
-        const bool groups32 = nt == 2 || nt == 6 || (nt == 4 && few);
-        // 16 inputs: by columns, but for 64k to 170k voxels and groups, where bricks
-        // are a little faster (96k voxels 10.6 us, columns 11.1; 160k: 12.9 and
-        // 13.5; 17k: 7.6 and 7.5, 11k: 7.8 and 6.6, 180k: 16.4 and 14.3, 1.6M: 74 and
-        // 48)
-        const long long nvg = nv * (Co / 32);
-        const bool mid = groups32 && nvg >= 64000 && nvg < 170000;
-        if (march_fits(g, Ci, Co) && nt % 2 == 0 && Ci == 16 && !accumulate && !mid) {
-            const long long cols = (long long)((g.W + 15) / 16) * ((g.H + 7) / 8) * g.B * (Co / 32);
-            const int n = march_planes(g, cols);
-            const long long items = cols * ((g.D + n - 1) / n);
-#define LAUNCH_PAIRS(OUT)                                                                        \
-    hipLaunchKernelGGL(k_conv_march_pairs<OUT>, dim3((unsigned)items), dim3(256), kMhLds, s, x, w, \
-                       bias, g, Co, n, alpha, act, y16, y32, ym)
-            if (ym) LAUNCH_PAIRS(kMaDz);
-            else if (y16 && y32) LAUNCH_PAIRS(kMaBoth);
-            else if (y32) LAUNCH_PAIRS(kMaF32);
-            else LAUNCH_PAIRS(kMaBf16);
-#undef LAUNCH_PAIRS
-        } else if (Ci == 16 && groups32) LAUNCH_REG(16, 2, 4);
-        else if (Ci == 32 && march_fits(g, Ci, Co) && !accumulate && nt % 2 == 0) {
-            const long long cols = (long long)((g.W + 15) / 16) * ((g.H + 7) / 8) * g.B * (Co / 32);
-            const int n = march_planes(g, cols);
-            const long long items = cols * ((g.D + n - 1) / n);
-#define LAUNCH_MARCH(OUT)                                                                     \
-    hipLaunchKernelGGL(k_conv_march<OUT>, dim3((unsigned)items), dim3(256), kMarchLds, s, x, w, \
-                       bias, g, Co, n, alpha, act, y16, y32, ym)
-            if (ym) LAUNCH_MARCH(kMaDz);
-            else if (y16 && y32) LAUNCH_MARCH(kMaBoth);
-            else if (y32) LAUNCH_MARCH(kMaF32);
-            else LAUNCH_MARCH(kMaBf16);
-#undef LAUNCH_MARCH
+        // groups of 32 outputs: by columns or bricks 32 and 96, and 64 when the
+        // bricks are too few to fill the device; by columns or from weight slabs
+        // (below) 64, 128 and 192
+        const bool groups32 = nt == 2 || nt == 6 || (nt == 4 && nbk < kFewBricks);
+        if ((Ci == 16 || Ci == 32) && nt % 2 == 0) {
+            const Route route = !march_fits(g, Ci, Co) || accumulate
+                                    ? (groups32 ? Route::kBricks : Route::kSlabs)
+                                    : route_few(g, Ci, Co, groups32);
+            if (route == Route::kBricks) {
+                if (Ci == 16) LAUNCH_REG(16, 2, 4);
+                else LAUNCH_REG(32, 2, 6);
+                return hipGetLastError();
+            }
+            if (route == Route::kColumns) {
+                const March m = plan_columns(g, Ci, Co);
+#define LAUNCH_COLUMNS(KERNEL, LDS)                                                             \
+    hipLaunchKernelGGL(KERNEL, dim3((unsigned)m.items), dim3(256), LDS, s, x, w, bias, g, Co,   \
+                       m.planes, alpha, act, y16, y32, ym)
+#define LAUNCH_OUT(OUT)                                                                         \
+    if (Ci == 16) LAUNCH_COLUMNS(k_conv_march_pairs<OUT>, kMhLds);                              \
+    else LAUNCH_COLUMNS(k_conv_march<OUT>, kMarchLds)
+                if (ym) { LAUNCH_OUT(kMaDz); }
+                else if (y16 && y32) { LAUNCH_OUT(kMaBoth); }
+                else if (y32) { LAUNCH_OUT(kMaF32); }
+                else { LAUNCH_OUT(kMaBf16); }
+#undef LAUNCH_OUT
+#undef LAUNCH_COLUMNS
+                return hipGetLastError();
+            }
         }
-        else done = false;
 #undef LAUNCH_REG
-        if (done) return hipGetLastError();
     }
     const bool few = (long long)((g.W + kRX - 1) / kRX) * ((g.H + kRY - 1) / kRY) *
                          ((g.D + kRZ - 1) / kRZ) * g.B < kFewBricks;

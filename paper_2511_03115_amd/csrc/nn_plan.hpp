@@ -59,5 +59,64 @@ inline WidePlan plan_wide(const Geo& g, int Co) {
     return best;
 }
 
+// ---- columns that march along z --------------------------------------------
+// n output planes each (a multiple of `multiple`, which divides D), one or two
+// workgroups to a CU: base + (n + 2) x shared for every 512 of them and
+// (n + 2) x alone or shared for what is left (32 -> 32, 4 x 64 x 32 x 32 voxels:
+// n = 8, 256 workgroups 20.2 us, n = 6, 352: 24.3, n = 4, 512: 20.9; 2 x 50 x 24 x
+// 40: n = 4, 234 workgroups 12.7, n = 2, 450: 13.9).
+struct March {
+    int planes;
+    long long items, cost;
+};
+inline March plan_march(int D, long long cols, int base, int alone, int shared, int multiple = 1) {
+    March best{D, cols, 1LL << 60};
+    const int U = D / multiple;
+    for (int u = U; u >= 1; --u) {
+        const int k = (int)ceil_div(U, u);
+        u = (int)ceil_div(U, k);   // the shortest columns of as many pieces
+        const long long items = cols * k;
+        const long long cost = base + (u * multiple + 2LL) * (shared * ((items - 1) / 512) +
+                                                              (last_round(items, 512) <= 256 ? alone : shared));
+        if (cost <= best.cost) best = March{u * multiple, items, cost};
+    }
+    return best;
+}
+
+// ---- 16 and 32 inputs, groups of 32 outputs --------------------------------
+// By columns (k_conv_march, k_conv_march_pairs), by bricks (k_conv_fwd_reg), or,
+// where the outputs are not taken 32 at a time, from weight slabs
+// (k_conv_fwd_lds).  Fits to 2 x 400 random shapes: 16 inputs 3.3 us + (n + 2) 1.05
+// alone, 1.55 shared; bricks 2.2 + 7.8 for every 768, 5.0, 6.8 or 8.6 for those
+// left; slabs 0.19 ns per voxel and 64 outputs, 14.4 at least.  32 inputs 1.8 +
+// (n + 2) 1.6 or 2.5; bricks 2.0 + 9.7 for every 512, 7.3 or 9.8; slabs 8 + 0.29
+// ns, 21.3 at least.  Columns are twice as fast where they are full (100 x 128 x
+// 128, 32 -> 32: 128 us by bricks, 78; 16 -> 32: 74 and 48); on volumes of one to
+// four rows, or narrower than a column, they are not (32 -> 32 on 300 x 1 x 79: 11.2
+// by bricks, 13.8; 16 -> 128 on 3 x 300 x 73 x 1: 33 from slabs, 96).
+enum class Route { kColumns, kBricks, kSlabs };
+inline March plan_columns(const Geo& g, int Ci, int Co) {
+    const long long cols = columns_of(g, 8) * (Co / 32);
+    return Ci == 16 ? plan_march(g.D, cols, 330, 105, 155) : plan_march(g.D, cols, 180, 160, 250);
+}
+inline Route route_few(const Geo& g, int Ci, int Co, bool groups32) {
+    const long long columns = plan_columns(g, Ci, Co).cost;
+    if (!groups32) {
+        const long long v = g.nvox() * Co / 64;
+        const long long slabs = Ci == 16 ? std::max(1440LL, 800 + v * 19 / 1000)
+                                         : std::max(2130LL, 800 + v * 29 / 1000);
+        return columns <= slabs ? Route::kColumns : Route::kSlabs;
+    }
+    const long long nb = bricks_of(g) * (Co / 32);
+    long long bricks;
+    if (Ci == 16) {
+        const long long l = last_round(nb, 768);
+        bricks = 220 + 780 * ((nb - 1) / 768) + (l <= 256 ? 500 : l <= 512 ? 680 : 860);
+    } else {
+        bricks = 200 + 970 * ((nb - 1) / 512) + (last_round(nb, 512) <= 256 ? 730 : 980);
+    }
+    return columns <= bricks ? Route::kColumns : Route::kBricks;
+}
+
 }  // namespace nn
 }  // namespace sde

@@ -40,8 +40,62 @@ static void wide() {
     }
 }
 
+static void few_inputs() {
+    const Route C = Route::kColumns, B = Route::kBricks, S = Route::kSlabs;
+    const char* const name[] = {"columns", "bricks", "slabs"};
+    struct {
+        Geo g;
+        int ci, co;
+        bool groups32;
+        Route route;
+    } at[] = {
+        {{1, 300, 1, 79}, 32, 32, true, B},     // 11.2 us, by columns 13.8
+        {{3, 14, 4, 295}, 32, 96, true, B},     // 19.0, 22.7
+        {{2, 300, 3, 25}, 32, 96, true, B},     // 21.6, 25.0
+        {{3, 30, 255, 3}, 32, 128, false, S},   // 50.9, 65.2
+        {{20, 218, 10, 3}, 32, 64, false, S},   // 47.3, 84.0
+        {{1, 100, 128, 128}, 32, 32, true, C},  // 78, by bricks 128
+        {{4, 64, 32, 32}, 32, 96, true, C},     // 49, 84
+        {{1, 100, 57, 57}, 32, 64, false, C},   // 56, from slabs 110
+        {{3, 300, 3, 1}, 16, 96, true, B},      // 10.3, 14.6
+        {{1, 172, 2, 149}, 16, 32, true, B},    // 8.8, 11.6
+        {{4, 99, 4, 298}, 16, 64, true, B},     // 45.0, 55.0
+        {{3, 16, 8, 253}, 16, 64, true, B},     // 11.9, 13.8
+        {{3, 300, 73, 1}, 16, 128, false, S},   // 33.1, 95.6
+        {{24, 61, 9, 6}, 16, 128, false, S},    // 34.8, 45.1
+        {{1, 100, 128, 128}, 16, 32, true, C},  // 48, by bricks 74
+    };
+    for (const auto& a : at) {
+        char what[90];
+        const Route got = route_few(a.g, a.ci, a.co, a.groups32);
+        std::snprintf(what, sizeof what, "%d -> %d, %d x %d x %d x %d: %s, %s wanted", a.ci, a.co,
+                      a.g.B, a.g.D, a.g.H, a.g.W, name[(int)got], name[(int)a.route]);
+        check(what, got == a.route);
+    }
+    // the split: every plane once, and no other split modelled as faster
+    for (int D = 1; D <= 120; ++D)
+        for (const long long cols : {1, 3, 64, 130, 257, 511, 513, 2000}) {
+            const March m = plan_march(D, cols, 180, 160, 250);
+            long long best = 1LL << 60;
+            for (int n = 1; n <= D; ++n) {
+                const long long it = cols * ceil_div(D, n);
+                best = std::min(best, 180 + (n + 2) * (250 * ((it - 1) / 512) +
+                                                       (last_round(it, 512) <= 256 ? 160 : 250)));
+            }
+            if (m.cost != best || m.items != cols * ceil_div(D, m.planes) || m.planes < 1 ||
+                m.planes > D)
+                check("a split into columns", false);
+            if (D % 2 == 0) {
+                const March e = plan_march(D, cols, 180, 160, 250, 2);
+                if (e.planes % 2 || e.items != cols * ceil_div(D, e.planes))
+                    check("a split into columns of even length", false);
+            }
+        }
+}
+
 int main() {
     wide();
+    few_inputs();
     std::printf("done: %d failures\n", failures);
     return failures ? 1 : 0;
 }

@@ -45,3 +45,12 @@ def _batch_equals_volumes(shape, ci, co):
     ((7, 33, 2, 18), 192, 64), ((17, 8, 8, 8), 64, 192)])
 def test_wide_inputs(shape, ci, co):
     _batch_equals_volumes(shape, ci, co)
+
+
+@pytest.mark.parametrize("shape,ci,co", [
+    ((9, 30, 3, 33), 32, 32), ((12, 20, 4, 50), 32, 96), ((5, 200, 9, 3), 32, 64),
+    ((9, 240, 10, 3), 32, 128), ((7, 20, 20, 19), 32, 32),
+    ((9, 30, 3, 33), 16, 32), ((12, 20, 4, 50), 16, 96), ((5, 200, 9, 3), 16, 64),
+    ((9, 240, 10, 2), 16, 128), ((7, 20, 20, 19), 16, 64)])
+def test_few_inputs(shape, ci, co):
+    _batch_equals_volumes(shape, ci, co)
