@@ -3812,42 +3812,12 @@ inline int blocks_for(long long n, int bs = 256, int cap = 16384) {
     return (int)g;
 }
 
-// Output planes per column (a multiple of `multiple`, which divides D) of
-// k_conv_march16: a workgroup's time is about that of n + 2 planes, 1.6 times as
-// long with two workgroups on a CU.
-int march_planes(const Geo& g, long long cols, int multiple = 1) {
-    long long best = 1LL << 60;
-    int pick = g.D;
-    for (int n = multiple; n <= g.D; n += multiple) {
-        const long long items = cols * ((g.D + n - 1) / n);
-        const long long cost = items <= 256 ? 10 * (n + 2) : 16 * (n + 2) * ((items + 511) / 512);
-        if (cost < best) {
-            best = cost;
-            pick = n;
-        }
-    }
-    return pick;
-}
-
 // The 16 -> 16 convolution by columns (groups of 16 outputs): 32-bit offsets,
-// kOob past every operand and past a plane of FP32 outputs; and from 2M voxels
-// and groups on (the persistent bricks of k_conv_rows have the shorter start:
-// 100 x 40 x 40 voxels 8.2 us, columns 9.8; 1.6M: 30.2 and 31.7; 2.1M: 36.0 and
-// 33.8; 3.3M: 53.6 and 47.9; 13.1M: 235 and 177).
-bool march16_takes(const Geo& g, int groups) {
-    return g.nvox() * 32 * groups <= kOob && (long long)g.H * g.W * 64 * groups <= kOob &&
-           g.nvox() * groups >= 1LL << 21;
-}
-
+// kOob past every operand and past a plane of FP32 outputs.
 template <int OUT>
-hipError_t launch_march16(const uint16_t* x, const uint16_t* w, const float* bias, const Geo& g,
-                          float alpha, int act, uint16_t* y16, float* y32, hipStream_t s,
-                          HeadArgs head, int groups) {
-    const long long cols = (long long)((g.W + 15) / 16) * ((g.H + 15) / 16) * g.B * groups;
-    const int n = march_planes(g, cols, OUT == kOutPool || OUT == kOutUpDz ? 2 : 1);
-    hipLaunchKernelGGL(k_conv_march16<OUT>, dim3((unsigned)(cols * ((g.D + n - 1) / n))), dim3(256),
-                       kM16Lds, s, x, w, bias, g, n, alpha, act, y16, y32, head, 16 * groups);
-    return hipGetLastError();
+bool march16_takes(const Geo& g, int groups, March* m) {
+    return g.nvox() * 32 * groups <= kOob && (long long)g.H * g.W * 64 * groups <= kOob &&
+           plan_march16(g, groups, OUT == kOutPool || OUT == kOutUpDz ? 2 : 1, m);
 }
 
 // The persistent row-reuse convolution: as many workgroups as the device
@@ -3858,9 +3828,14 @@ hipError_t launch_rows_as(const uint16_t* x, const uint16_t* xl, const uint16_t*
                           const float* bias, Geo g, float alpha, int act, uint16_t* y16,
                           float* y32, int accumulate, hipStream_t s, HeadArgs head = {},
                           int groups = 1) {
-    if constexpr (CI == 16)
-        if (march16_takes(g, groups) && !accumulate)
-            return launch_march16<OUT>(x, w, bias, g, alpha, act, y16, y32, s, head, groups);
+    if constexpr (CI == 16) {
+        March m;
+        if (!accumulate && march16_takes<OUT>(g, groups, &m)) {
+            hipLaunchKernelGGL(k_conv_march16<OUT>, dim3((unsigned)m.items), dim3(256), kM16Lds, s, x,
+                               w, bias, g, m.planes, alpha, act, y16, y32, head, 16 * groups);
+            return hipGetLastError();
+        }
+    }
     constexpr bool F32 = OUT == kOutF32;
     constexpr size_t lds = ((size_t)kRVox * brick_row(CI) + 256 * 8) * sizeof(uint16_t);
     static const int cap = [] {

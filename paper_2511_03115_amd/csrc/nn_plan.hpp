@@ -118,5 +118,22 @@ inline Route route_few(const Geo& g, int Ci, int Co, bool groups32) {
     return columns <= bricks ? Route::kColumns : Route::kBricks;
 }
 
+// ---- 16 inputs, 1 to 3 groups of 16 outputs ---------------------------------
+// k_conv_march16's columns of 16 x 16 voxels, from 2M voxels and groups on (the
+// persistent bricks of k_conv_rows have the shorter start: 100 x 40 x 40 voxels
+// 8.2 us, columns 9.8; 1.6M: 30.2 and 31.7; 2.1M: 36.0 and 33.8; 13.1M: 235 and
+// 177) and where their modelled time is the less by 6 %: 4.1 ns per brick, three
+// groups 3.3 ps per voxel and group more, against (n + 2) planes of 1.01 or 1.62 us
+// (fits to 2 x 450 random shapes).  On few rows most of a column lies beside the
+// volume: 16 -> 48 on 4 x 300 x 4 x 255 65 us by bricks, 153 by columns; 16 -> 16 on 2
+// x 111 x 89 x 136 46 and 52.
+inline bool plan_march16(const Geo& g, int groups, int multiple, March* m) {
+    const long long v = g.nvox() * groups;
+    if (v < 1LL << 21) return false;
+    *m = plan_march(g.D, columns_of(g, 16) * groups, 300, 101, 162, multiple);
+    const long long rows = 300 + bricks_of(g) * groups * 41 / 100 + (groups > 2 ? v * 33 / 100000 : 0);
+    return m->cost * 106 < rows * 100 && m->items < 1LL << 24;   // (a launch is below 2^32 threads)
+}
+
 }  // namespace nn
 }  // namespace sde

@@ -93,9 +93,38 @@ static void few_inputs() {
         }
 }
 
+static void sixteen() {
+    struct {
+        Geo g;
+        int groups;
+        bool columns;
+    } at[] = {
+        {{4, 300, 4, 255}, 3, false},    // by bricks 65 us, by columns 153
+        {{25, 220, 8, 19}, 3, false},    // 62, 106
+        {{27, 259, 19, 19}, 1, false},   // 62, 88
+        {{2, 111, 89, 136}, 1, false},   // 46, 52
+        {{1, 259, 119, 176}, 3, true},   // 775, 279
+        {{4, 111, 59, 31}, 3, true},     // 59, 39
+        {{1, 200, 256, 256}, 1, true},   // 235, 177
+        {{4, 128, 64, 64}, 1, true},     // 36.0, 33.8
+        {{1, 100, 40, 40}, 1, false},    // 8.2, 9.8
+        {{1 << 25, 1, 1, 1}, 1, false},  // more columns than a launch has workgroups
+        {{1 << 22, 1, 2, 2}, 1, false},
+    };
+    for (const auto& a : at) {
+        char what[90];
+        March m;
+        const bool got = plan_march16(a.g, a.groups, 1, &m);
+        std::snprintf(what, sizeof what, "16 -> %d, %d x %d x %d x %d: by %s", 16 * a.groups, a.g.B,
+                      a.g.D, a.g.H, a.g.W, a.columns ? "columns" : "bricks");
+        check(what, got == a.columns && (!got || m.items < (1 << 24)));
+    }
+}
+
 int main() {
     wide();
     few_inputs();
+    sixteen();
     std::printf("done: %d failures\n", failures);
     return failures ? 1 : 0;
 }

@@ -1,7 +1,8 @@
 """A batch goes by other kernels, or in other blocks, than its volumes one by
 one: the same outputs, bit for bit, and within FP32 rounding of the definition,
 at sizes on both sides of the rules (volumes of few rows, few planes, few
-columns)."""
+columns).  16 -> 16 by columns needs 2M voxels: there a batch of small
+volumes against the volumes by bricks, with every output the network uses."""
 
 import numpy as np
 import pytest
@@ -54,3 +55,55 @@ def test_wide_inputs(shape, ci, co):
     ((9, 240, 10, 2), 16, 128), ((7, 20, 20, 19), 16, 64)])
 def test_few_inputs(shape, ci, co):
     _batch_equals_volumes(shape, ci, co)
+
+
+@pytest.mark.parametrize("B,D,H,W,co", [(65, 21, 45, 47, 16), (160, 9, 31, 49, 16),
+                                        (22, 21, 46, 47, 48), (25, 90, 20, 8, 48)])
+def test_sixteen_inputs(B, D, H, W, co):
+    import torch
+    from paper_2511_03115_amd import nn
+    assert B * D * H * W * (co // 16) >= 1 << 20
+    log(f"conv routes 16 -> {co} {(B, D, H, W)}")
+    gen = torch.Generator(device="cuda").manual_seed(D)
+    x = torch.randn((B, D, H, W, 16), generator=gen, device="cuda").bfloat16()
+    w = (0.1 * torch.randn((co, 27, 16), generator=gen, device="cuda")).bfloat16()
+    b = torch.randn(co, generator=gen, device="cuda")
+    empty = lambda n, dt: torch.full((n, D, H, W, co), float("nan"), dtype=dt, device="cuda")
+    y16, y32, only = empty(B, torch.bfloat16), empty(B, torch.float32), empty(B, torch.bfloat16)
+    nn.conv3d_fwd(x, w, b, act=True, alpha=0.1, out16=y16, out32=y32)
+    nn.conv3d_fwd(x, w, b, act=True, alpha=0.1, out16=only)
+    assert torch.equal(y16, only)
+    for k in (0, 1, B // 2, B - 1):
+        s16, s32 = empty(1, torch.bfloat16), empty(1, torch.float32)
+        nn.conv3d_fwd(x[k:k + 1], w, b, act=True, alpha=0.1, out16=s16, out32=s32)
+        assert torch.equal(y16[k:k + 1], s16) and torch.equal(y32[k:k + 1], s32)
+
+
+@pytest.mark.parametrize("B,D,H,W", [(40, 22, 46, 62), (34, 30, 46, 46)])
+def test_network_on_copies(B, D, H, W):
+    """Copies of a volume: the same outputs as the volume alone, and its
+    gradient up to the order of the FP32 sums."""
+    import torch
+    from paper_2511_03115_amd import nn
+    from test_gpu_nn import _net_inputs, he_params
+    log(f"conv routes network {(B, D, H, W)}")
+    flat = nno.flatten(he_params(2, 16, 16, seed=9), 2, 16, 16).astype(np.float32)
+    one = _net_inputs(1, D, H, W, seed=8)
+    outs, grads = [], []
+    for n in (1, B):
+        net = nn.Net(2, 16, 16, 0.01, max_batch=n, max_dims=(D, H, W), train=True)
+        net.set_params(flat)
+        dev = [torch.from_numpy(np.repeat(a, n, axis=0)).cuda() for a in one]
+        out = torch.zeros((n, D, H, W), dtype=torch.float32, device="cuda")
+        net.forward(dev[0], dev[1], out)
+        outs.append(out)
+        net.loss_grad(*dev)
+        grads.append(np.array(net.get_grads(), dtype=np.float64))
+        net.close()
+    for k in range(B):
+        assert torch.equal(outs[1][k], outs[0][0])
+    # 1 / B in the loss is no power of two: the bf16 layer gradients round
+    # differently, to 2^-9 each; their sums over B D H W voxels stay within that
+    e = np.abs(grads[1] - grads[0]).max() / np.abs(grads[0]).max()
+    log(f"  gradient rel diff {e:.2e}")
+    assert e <= 2.0 ** -8
