@@ -4087,15 +4087,13 @@ hipError_t conv_cat_fwd(const uint16_t* skip, const uint16_t* low, const uint16_
     if (Co == 32 || Co == 64)
         return conv_wide(skip, low, w, bias, g, Cs + Cu, Cs, Co, alpha, act, y16, nullptr, 0,
                          nullptr, s);
-    if (g.nvox() * 32 <= kOob) {
+    int n = 0;
+    if (plan_cat16(g, &n)) {
         static const hipError_t attr = hipFuncSetAttribute(
             (const void*)k_conv_cat16, hipFuncAttributeMaxDynamicSharedMemorySize, kCatLds);
         if (attr != hipSuccess) return attr;
-        const long long cols = (long long)((g.W + 15) / 16) * ((g.H + 15) / 16) * g.B;
-        const long long nz = std::max(1LL, std::min((long long)g.D, 256 / cols));
-        const int n = (int)((g.D + nz - 1) / nz);
-        hipLaunchKernelGGL(k_conv_cat16, dim3((unsigned)(cols * ((g.D + n - 1) / n))), dim3(256),
-                           kCatLds, s, skip, low, w, bias, g, n, alpha, act, y16);
+        hipLaunchKernelGGL(k_conv_cat16, dim3((unsigned)(columns_of(g, 16) * ceil_div(g.D, n))),
+                           dim3(256), kCatLds, s, skip, low, w, bias, g, n, alpha, act, y16);
         return hipGetLastError();
     }
     return launch_rows<48, 16>(skip, low, w, bias, g, alpha, act, y16, nullptr, 0, s);

@@ -135,5 +135,30 @@ inline bool plan_march16(const Geo& g, int groups, int multiple, March* m) {
     return m->cost * 106 < rows * 100 && m->items < 1LL << 24;   // (a launch is below 2^32 threads)
 }
 
+// ---- the decoder's level-0 concatenation, 16 + 32 -> 16 ---------------------
+// k_conv_cat16's columns of 16 x 16 voxels, one workgroup to a CU: as many planes
+// each as make ceil(workgroups / 256) (n + 2), its time in units of 2.0 us, the
+// least; where that, with 3 us, is less than 3.5 us for every 256 bricks of the
+// persistent k_conv_rows.  As many columns' pieces as CUs, without a look at
+// the rest, left them idle (differences to the bricks' whole forward pass: 192 x
+// 192 x 200 voxels, 144 columns, -38 us in columns of 200 planes, -143 of 29; 264 x
+// 264 x 200, 289 columns, -38 and -285; 256 x 256 x 200, of 200, -290), and small
+// volumes are faster by bricks (2 x 100 x 8 x 200: +8 us by columns, 4 x 128 x 16 x 16
+// +2, 80 x 80 x 40 +1; 72 x 72 x 200 -15).
+inline bool plan_cat16(const Geo& g, int* planes) {
+    const long long cols = columns_of(g, 16);
+    long long best = 1LL << 60;
+    for (int n = g.D; n >= 1; --n) {
+        const int k = (int)ceil_div(g.D, n);
+        n = (int)ceil_div(g.D, k);
+        const long long c = ceil_div(cols * k, 256) * (n + 2);
+        if (c <= best) {
+            best = c;
+            *planes = n;
+        }
+    }
+    return 200 * best + 300 < 350 * ceil_div(bricks_of(g), 256);
+}
+
 }  // namespace nn
 }  // namespace sde

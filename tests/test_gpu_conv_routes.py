@@ -107,3 +107,27 @@ def test_network_on_copies(B, D, H, W):
     e = np.abs(grads[1] - grads[0]).max() / np.abs(grads[0]).max()
     log(f"  gradient rel diff {e:.2e}")
     assert e <= 2.0 ** -8
+
+
+@pytest.mark.parametrize("B,D,H,W", [(1, 24, 258, 262), (8, 14, 90, 92), (1, 200, 72, 72),
+                                     (1, 96, 130, 120), (2, 20, 8, 66), (1, 30, 82, 80)])
+def test_concatenation(B, D, H, W):
+    """The level-0 decoder convolution over the skip and the level below in
+    place, in long and in short columns and by bricks, against the stored
+    concatenation's: equal bit for bit."""
+    import torch
+    from paper_2511_03115_amd import nn
+    from test_gpu_nn import _net_inputs, he_params
+    log(f"conv routes concatenation {(B, D, H, W)}")
+    flat = nno.flatten(he_params(2, 16, 16, seed=3), 2, 16, 16).astype(np.float32)
+    dose, rho, _, _ = _net_inputs(B, D, H, W, seed=4)
+    outs = []
+    for stored in (False, True):
+        net = nn.Net(2, 16, 16, 0.01, max_batch=B, max_dims=(D, H, W), train=False,
+                     store_concat=stored)
+        net.set_params(flat)
+        out = torch.zeros((B, D, H, W), dtype=torch.float32, device="cuda")
+        net.forward(torch.from_numpy(dose).cuda(), torch.from_numpy(rho).cuda(), out)
+        outs.append(out.cpu().numpy())
+        net.close()
+    assert np.isfinite(outs[0]).all() and np.array_equal(*outs)
