@@ -3816,8 +3816,9 @@ inline int blocks_for(long long n, int bs = 256, int cap = 16384) {
 // kOob past every operand and past a plane of FP32 outputs.
 template <int OUT>
 bool march16_takes(const Geo& g, int groups, March* m) {
+    constexpr bool blocks = OUT == kOutPool || OUT == kOutUpDz;
     return g.nvox() * 32 * groups <= kOob && (long long)g.H * g.W * 64 * groups <= kOob &&
-           plan_march16(g, groups, OUT == kOutPool || OUT == kOutUpDz ? 2 : 1, m);
+           plan_march16(g, groups, blocks ? 2 : 1, blocks || OUT == kOutDz, m);
 }
 
 // The persistent row-reuse convolution: as many workgroups as the device

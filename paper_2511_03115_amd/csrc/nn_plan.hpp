@@ -126,13 +126,16 @@ inline Route route_few(const Geo& g, int Ci, int Co, bool groups32) {
 // groups 3.3 ps per voxel and group more, against (n + 2) planes of 1.01 or 1.62 us
 // (fits to 2 x 450 random shapes).  On few rows most of a column lies beside the
 // volume: 16 -> 48 on 4 x 300 x 4 x 255 65 us by bricks, 153 by columns; 16 -> 16 on 2
-// x 111 x 89 x 136 46 and 52.
-inline bool plan_march16(const Geo& g, int groups, int multiple, March* m) {
+// x 111 x 89 x 136 46 and 52.  Columns add the 2 x 2 x 2 sums of their planes in
+// registers and read the activations of a gradient ahead: with such outputs (fused)
+// they may be modelled 8 % the slower (pooled, 120 x 136 x 136: 54 us by bricks, 45;
+// a training step of 2 x 200 x 50 x 120 17 us less by columns).
+inline bool plan_march16(const Geo& g, int groups, int multiple, bool fused, March* m) {
     const long long v = g.nvox() * groups;
     if (v < 1LL << 21) return false;
     *m = plan_march(g.D, columns_of(g, 16) * groups, 300, 101, 162, multiple);
     const long long rows = 300 + bricks_of(g) * groups * 41 / 100 + (groups > 2 ? v * 33 / 100000 : 0);
-    return m->cost * 106 < rows * 100 && m->items < 1LL << 24;   // (a launch is below 2^32 threads)
+    return m->cost * (fused ? 92 : 106) < rows * 100 && m->items < 1LL << 24;   // (a launch is below 2^32 threads)
 }
 
 // ---- the decoder's level-0 concatenation, 16 + 32 -> 16 ---------------------

@@ -114,11 +114,13 @@ static void sixteen() {
     for (const auto& a : at) {
         char what[90];
         March m;
-        const bool got = plan_march16(a.g, a.groups, 1, &m);
+        const bool got = plan_march16(a.g, a.groups, 1, false, &m);
         std::snprintf(what, sizeof what, "16 -> %d, %d x %d x %d x %d: by %s", 16 * a.groups, a.g.B,
                       a.g.D, a.g.H, a.g.W, a.columns ? "columns" : "bricks");
         check(what, got == a.columns && (!got || m.items < (1 << 24)));
     }
+    March m;   // pooled: 54 us by bricks, 45 by columns
+    check("pooled 120 x 136 x 136: by columns", plan_march16({1, 120, 136, 136}, 1, 2, true, &m));
 }
 
 static void concatenation() {
