@@ -2638,8 +2638,8 @@ k_conv_march16(const uint16_t* __restrict__ x, const uint16_t* __restrict__ w,
 }
 
 // ---------------------------------------------------------------------------
-// Weight and bias gradients where an operand has 2 GiB or more, split over
-// voxel chunks:
+// Weight and bias gradients where an operand has 2 GiB or more, or where columns
+// lie mostly beside the volume (wgrad_by_slices), split over voxel chunks:
 //   part[c][t][co][ci] = sum_{v in chunk c} dz[v][co] x[shift(v, t)][ci],
 //   part_b[c][co]      = sum_{v in chunk c} dz[v][co].
 // Workgroup = (chunk, group of tg taps).  64-voxel slices of dz and of the
@@ -4234,33 +4234,6 @@ bool wgrad_by_bricks(const Geo& g, int Ci, int Co) {
     return (Co == 16 || Co == 32) && g.nvox() * (Ci / 16) * (Co / 16) < 80000;
 }
 
-// The split of k_wgrad_cols: n planes per column, ncol columns, cpw pairs of
-// columns per half workgroup, used workgroups per channel block.
-constexpr int kWgColsR = 2;
-struct WgradCols {
-    int n, ncol, cpw, used;
-};
-WgradCols wgrad_cols_plan(const Geo& g, int Ci, int Co, long long max_used) {
-    const int RY = 4 * kWgColsR;
-    const long long nxy = (long long)((g.W + 15) / 16) * ((g.H + RY - 1) / RY) * g.B;
-    // one workgroup per CU in all, as far as the partial sums' buffer goes
-    const long long want =
-        std::max(1LL, std::min(max_used, 256LL / std::max(1, (Ci / 16) * (Co / 16))));
-    // the plane count whose longest workgroup marches over the fewest planes
-    // (of equals the longest columns)
-    WgradCols p{};
-    long long best = 1LL << 60;
-    for (int nz = 1; nz <= std::min(g.D, 64); ++nz) {
-        const int n = (g.D + nz - 1) / nz;
-        const long long ncol = nxy * ((g.D + n - 1) / n), pairs = (ncol + 1) / 2;
-        const long long cpw = (pairs + 2 * want - 1) / (2 * want);
-        if (ncol > (1 << 29) || cpw * (n + 2) >= best) continue;
-        best = cpw * (n + 2);
-        p = WgradCols{n, (int)ncol, (int)cpw, (int)((pairs + 2 * cpw - 1) / (2 * cpw))};
-    }
-    return p;
-}
-
 // dw and db (nullable) from nrow rows of partial sums, outputs in groups of cg
 hipError_t colsum_wb(const float* part, const float* part_b, int nrow, int Ci, int Co, int cg,
                      float* dw, float* db, hipStream_t s, int frag = 0) {
@@ -4295,8 +4268,9 @@ hipError_t wgrad_impl(const uint16_t* dz, const uint16_t* x, const uint16_t* xl,
         }();
         if (attr != hipSuccess) return attr;
     }
-    if (wgrad_buffers(g, Ci, Co) && !wgrad_by_bricks(g, Ci, Co)) {
-        const WgradCols wc = wgrad_cols_plan(g, Ci, Co, nchunk);
+    const bool bricks = wgrad_buffers(g, Ci, Co) && wgrad_by_bricks(g, Ci, Co);
+    const WgradCols wc = bricks ? WgradCols{} : wgrad_cols_plan(g, Ci, Co, nchunk);
+    if (wgrad_buffers(g, Ci, Co) && !bricks && !wgrad_by_slices(g, Ci, Co, wc)) {
         float* part_b = part + (size_t)wc.used * 27 * Co * Ci;
         const unsigned grid = (unsigned)(wc.used * (Ci / 16) * (Co / 16) + 7) / 8 * 8;
         hipLaunchKernelGGL(k_wgrad_cols<kWgColsR>, dim3(grid), dim3(512),
@@ -4306,8 +4280,7 @@ hipError_t wgrad_impl(const uint16_t* dz, const uint16_t* x, const uint16_t* xl,
         if (e != hipSuccess) return e;
         return colsum_wb(part, part_b, wc.used, Ci, Co, 16, dw, db, s, 1);
     }
-    if (wgrad_buffers(g, Ci, Co)) {
-        // by bricks, within the same partial-sum buffer
+    if (bricks) {   // within the same partial-sum buffer
         const long long nbk = (long long)((g.W + kRX - 1) / kRX) * ((g.H + kRY - 1) / kRY) *
                               ((g.D + kRZ - 1) / kRZ) * g.B;
         // about 512 workgroups per launch (two per CU, one round): fewer

@@ -163,5 +163,46 @@ inline bool plan_cat16(const Geo& g, int* planes) {
     return 200 * best + 300 < 350 * ceil_div(bricks_of(g), 256);
 }
 
+// ---- weight gradients -------------------------------------------------------
+// The split of k_wgrad_cols: n planes per column, ncol columns, cpw pairs of
+// columns per half workgroup, used workgroups per channel block.
+constexpr int kWgColsR = 2;
+struct WgradCols {
+    int n, ncol, cpw, used;
+};
+inline WgradCols wgrad_cols_plan(const Geo& g, int Ci, int Co, long long max_used) {
+    const long long nxy = columns_of(g, 4 * kWgColsR);
+    // one workgroup per CU in all, as far as the partial sums' buffer goes
+    const long long want =
+        std::max(1LL, std::min(max_used, 256LL / std::max(1, (Ci / 16) * (Co / 16))));
+    // the plane count whose longest workgroup marches over the fewest planes
+    // (of equals the longest columns)
+    WgradCols p{};
+    long long best = 1LL << 60;
+    for (int nz = 1; nz <= std::min(g.D, 64); ++nz) {
+        const int n = (int)ceil_div(g.D, nz);
+        const long long ncol = nxy * ceil_div(g.D, n), pairs = (ncol + 1) / 2;
+        const long long cpw = ceil_div(pairs, 2 * want);
+        if (ncol > (1 << 29) || cpw * (n + 2) >= best) continue;
+        best = cpw * (n + 2);
+        p = WgradCols{n, (int)ncol, (int)cpw, (int)ceil_div(pairs, 2 * cpw)};
+    }
+    return p;
+}
+
+// Output widths other than 16, 32, 64 and 128 (which have never gone by them)
+// take k_wgrad_partial's 64-voxel slices where a column is mostly beside the
+// volume: columns 10.0 us, 1.3 for each plane a workgroup marches over and their
+// partial sums' bytes at 2 TB/s there and back; slices 14 us + 0.22 ns, or 30 + 0.085,
+// per voxel and channel block (fits to 2 x 100 random shapes; 16 -> 192 on 2 x 300 x 1
+// x 1 31 us by columns, 14 from slices; 128 -> 96 on 41 x 50 x 2 x 4 175 and 91; 96 -> 96
+// on 1 x 35 x 38 x 18 38 and 86).
+inline bool wgrad_by_slices(const Geo& g, int Ci, int Co, const WgradCols& p) {
+    if (Co == 16 || Co == 32 || Co == 64 || Co == 128) return false;
+    const long long v = g.nvox() * (Ci / 16) * (Co / 16);
+    const long long columns = 1000 + 130LL * p.cpw * (p.n + 2) + p.used * 27LL * Ci * Co / 5000;
+    return std::min(1400 + v * 22 / 1000, 3000 + v * 85 / 10000) < columns;
+}
+
 }  // namespace nn
 }  // namespace sde

@@ -151,8 +151,32 @@ static void concatenation() {
     }
 }
 
+static void weight_gradients() {
+    struct {
+        Geo g;
+        int ci, co;
+        bool slices;
+    } at[] = {
+        {{2, 300, 1, 1}, 16, 192, true},     // 14.3 us, by columns 31.3
+        {{41, 50, 2, 4}, 128, 96, true},     // 91, 175
+        {{16, 300, 1, 4}, 32, 48, true},     // 44, 51
+        {{1, 300, 7, 1}, 16, 96, true},      // 16.4, 19.5
+        {{1, 35, 38, 18}, 96, 96, false},    // 86, 38
+        {{2, 300, 70, 2}, 32, 96, false},    // 192, 102
+        {{2, 300, 1, 1}, 16, 64, false},     // bricks before: columns
+    };
+    for (const auto& a : at) {
+        char what[90];
+        const bool got = wgrad_by_slices(a.g, a.ci, a.co, wgrad_cols_plan(a.g, a.ci, a.co, 1000));
+        std::snprintf(what, sizeof what, "weight gradient %d -> %d, %d x %d x %d x %d: %s", a.ci, a.co,
+                      a.g.B, a.g.D, a.g.H, a.g.W, a.slices ? "slices" : "columns");
+        check(what, got == a.slices);
+    }
+}
+
 int main() {
     wide();
+    weight_gradients();
     concatenation();
     few_inputs();
     sixteen();
