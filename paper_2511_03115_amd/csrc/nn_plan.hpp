@@ -26,6 +26,9 @@ inline long long columns_of(const Geo& g, int ry) {
     return ceil_div(g.W, 16) * ceil_div(g.H, ry) * g.B;
 }
 
+// a launch is below 2^32 threads, 256 to a workgroup
+constexpr long long kMaxItems = (1LL << 24) - 1;
+
 // Workgroups beyond whole rounds of `round`: 1..round of them.
 inline long long last_round(long long items, long long round) {
     return items - (items - 1) / round * round;
@@ -52,9 +55,9 @@ inline WidePlan plan_wide(const Geo& g, int Co) {
     WidePlan best{0, 790 * ((nb - 1) / 512) + (last_round(nb, 512) <= 256 ? 500 : 710)};
     const int planes[3] = {1, 2, 4}, time[3] = {300, 365, 510}, start[3] = {0, 0, 45};
     for (int k = 2; k >= 0; --k) {
-        const long long c =
-            time[k] * ceil_div(cols * ceil_div(g.D, planes[k]), 256) + start[k];
-        if (c <= best.cost) best = WidePlan{planes[k], c};
+        const long long items = cols * ceil_div(g.D, planes[k]);
+        const long long c = time[k] * ceil_div(items, 256) + start[k];
+        if (c <= best.cost && items <= kMaxItems) best = WidePlan{planes[k], c};
     }
     return best;
 }
@@ -62,7 +65,8 @@ inline WidePlan plan_wide(const Geo& g, int Co) {
 // ---- columns that march along z --------------------------------------------
 // n output planes each (a multiple of `multiple`, which divides D), one or two
 // workgroups to a CU: base + (n + 2) x shared for every 512 of them and
-// (n + 2) x alone or shared for what is left (32 -> 32, 4 x 64 x 32 x 32 voxels:
+// (n + 2) x alone or shared for what is left; without end where no split is few
+// enough for a launch (32 -> 32, 4 x 64 x 32 x 32 voxels:
 // n = 8, 256 workgroups 20.2 us, n = 6, 352: 24.3, n = 4, 512: 20.9; 2 x 50 x 24 x
 // 40: n = 4, 234 workgroups 12.7, n = 2, 450: 13.9).
 struct March {
@@ -78,7 +82,7 @@ inline March plan_march(int D, long long cols, int base, int alone, int shared, 
         const long long items = cols * k;
         const long long cost = base + (u * multiple + 2LL) * (shared * ((items - 1) / 512) +
                                                               (last_round(items, 512) <= 256 ? alone : shared));
-        if (cost <= best.cost) best = March{u * multiple, items, cost};
+        if (cost <= best.cost && items <= kMaxItems) best = March{u * multiple, items, cost};
     }
     return best;
 }
@@ -135,7 +139,7 @@ inline bool plan_march16(const Geo& g, int groups, int multiple, bool fused, Mar
     if (v < 1LL << 21) return false;
     *m = plan_march(g.D, columns_of(g, 16) * groups, 300, 101, 162, multiple);
     const long long rows = 300 + bricks_of(g) * groups * 41 / 100 + (groups > 2 ? v * 33 / 100000 : 0);
-    return m->cost * (fused ? 92 : 106) < rows * 100 && m->items < 1LL << 24;   // (a launch is below 2^32 threads)
+    return m->cost < 1LL << 40 && m->cost * (fused ? 92 : 106) < rows * 100;
 }
 
 // ---- the decoder's level-0 concatenation, 16 + 32 -> 16 ---------------------

@@ -72,6 +72,10 @@ static void few_inputs() {
                       a.g.B, a.g.D, a.g.H, a.g.W, name[(int)got], name[(int)a.route]);
         check(what, got == a.route);
     }
+    // a batch of single voxels: more columns than a launch has workgroups
+    check("10M volumes, 64 -> 64: by bricks", plan_wide({10000000, 1, 1, 1}, 64).planes == 0);
+    check("10M volumes, 32 -> 64: from slabs", route_few({10000000, 1, 1, 1}, 32, 64, false) == S);
+    check("10M volumes, 16 -> 96: by bricks", route_few({10000000, 1, 1, 1}, 16, 96, true) == B);
     // the split: every plane once, and no other split modelled as faster
     for (int D = 1; D <= 120; ++D)
         for (const long long cols : {1, 3, 64, 130, 257, 511, 513, 2000}) {
