@@ -7,7 +7,9 @@ import subprocess
 
 import pytest
 
-from test_sanitizers import CSRC, ROCM, ROOT
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2511_03115_amd", "csrc")
+ROCM = "/opt/rocm"
 
 
 @pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not available")
