@@ -12,9 +12,11 @@ namespace nn {
 // 3x3x3 conv, zero padding 1; y = act(conv(x, w) + bias) to bf16 y16 and/or
 // FP32 y32 (y32 += result when accumulate).  Ci % 16 == 0, Co % 16 == 0 and
 // Co / 16 in {1, 2, 3, 4, 6, 8, 12}.  bias may be null; act = LeakyReLU(alpha).
-// The kernel is chosen by the channel counts: registers-held weights for
-// Ci <= 48 with 16 or 32 outputs, 32-channel passes for Ci >= 64 with 32 or
-// 64, LDS weight slabs otherwise.
+// The kernel is chosen by the channel counts and, among those that take them, by
+// modelled time (nn_plan.hpp): for 16 outputs of up to 48 inputs persistent
+// bricks, from 2M voxels on columns that march along z; for groups of 32 outputs
+// columns or bricks (16 or 32 inputs), blocks of planes or bricks in 32-channel
+// passes (64 and more); LDS weight slabs or halo bricks otherwise.
 //
 // With ym non-null (bias, act, accumulate and y32 zero) y16 gets instead the
 // input gradient of a LeakyReLU layer whose output is ym (Co channels):
@@ -82,8 +84,9 @@ hipError_t flip_transpose(const uint16_t* w, uint16_t* wt, int Ci, int Co, hipSt
 // (nullable).  Ci % 16 == 0, Co % 16 == 0, (Co/16)(Ci/16) <= 64, chunk from
 // wgrad_chunk_for (a multiple of 64).  By 16 x 8 voxel columns along z, or by
 // 4 x 4 x 16 bricks (the smallest layers with 16 or 32 outputs), with at most as
-// many split-K chunks as the chunk length gives; operands of 2 GiB and more by
-// 64-voxel slices and tap groups.
+// many split-K chunks as the chunk length gives; other widths on volumes that
+// columns hardly cover, and operands of 2 GiB and more, by 64-voxel slices and
+// tap groups.
 long long wgrad_chunks(const int* dims, int chunk);
 int wgrad_chunk_for(const int* dims, int Ci, int Co, long long max_part_floats);
 long long wgrad_part_floats(const int* dims, int Ci, int Co, int chunk);
