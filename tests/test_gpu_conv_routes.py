@@ -131,3 +131,29 @@ def test_concatenation(B, D, H, W):
         outs.append(out.cpu().numpy())
         net.close()
     assert np.isfinite(outs[0]).all() and np.array_equal(*outs)
+
+
+@pytest.mark.parametrize("levels,B,D,H,W", [(3, 2, 80, 8, 24), (4, 1, 16, 16, 104), (3, 5, 24, 16, 8)])
+def test_training_of_few_rows(levels, B, D, H, W):
+    """Networks whose lower levels have one to four rows: with the decoder's
+    concatenations read in place and stored, equal bit for bit in outputs, loss and
+    gradients."""
+    import torch
+    from paper_2511_03115_amd import nn
+    from test_gpu_nn import _net_inputs, he_params
+    log(f"conv routes training levels={levels} {(B, D, H, W)}")
+    flat = nno.flatten(he_params(levels, 16, 16, seed=5), levels, 16, 16).astype(np.float32)
+    dev = [torch.from_numpy(a).cuda() for a in _net_inputs(B, D, H, W, seed=6)]
+    got = []
+    for stored in (False, True):
+        net = nn.Net(levels, 16, 16, 0.01, max_batch=B, max_dims=(D, H, W), train=True,
+                     store_concat=stored)
+        net.set_params(flat)
+        out = torch.zeros((B, D, H, W), dtype=torch.float32, device="cuda")
+        net.forward(dev[0], dev[1], out)
+        loss = net.loss_grad(*dev)
+        got.append((out.cpu().numpy(), loss, net.get_grads().copy()))
+        net.close()
+    (o0, l0, g0), (o1, l1, g1) = got
+    assert np.isfinite(o0).all() and np.abs(g0).max() > 0
+    assert np.array_equal(o0, o1) and l0 == l1 and np.array_equal(g0, g1)
